@@ -182,9 +182,8 @@ int sva_select_blocks(const sva_problem* prob, const sva_select_params* sel,
  * whose row sums would overflow float32 (logits rising by more than about
  * 2^63 within one kept block), whose inputs hold Inf or NaN, or, at block 64
  * with D = 128 and long rows, whose pair of lists is not strictly increasing
- * and in range, is marked through its output and redone by a per-block
- * rescaling kernel on a small grid (correct, but many times slower per
- * block).  Lists as sva_select_blocks writes them never take that path. */
+ * and in range, is walked again by its workgroup with a running maximum
+ * (correct, but several times slower per block).  Lists as sva_select_blocks writes them never take that path. */
 int sva_sparse_attention(const sva_problem* prob, const void* q, const void* k,
                          const void* v, const int32_t* kv_idx,
                          const int32_t* kv_count, int32_t kmax, void* out,

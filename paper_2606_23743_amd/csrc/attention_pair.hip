@@ -14,9 +14,9 @@
 // The union is built in LDS from two bitmaps over the key blocks, which needs
 // lists that are strictly increasing and in range, as the selection kernel
 // writes them.  A pair with any other list (out-of-range entries, repeats,
-// another order) is marked (NaN first output element of both blocks) and the
-// per-iteration rescaling kernel that runs next recomputes it with the general
-// list semantics.  Per chunk, the arithmetic of a wave is that of the
+// another order) skips the union and walks its two lists one after the other
+// with the general list semantics (general_walk16), as does a pair with a
+// query whose sum overflows.  Per chunk, the arithmetic of a wave is that of the
 // 32-query kernel (attn_w16.h: Sᵀ = K·Qᵀ on 16x16x32 products, fixed reference
 // maximum from the wave's first chunk, P rounded to bf16 with l summed from
 // it, Oᵀ += Vᵀ·Pᵀ), so keep-all lists give dense attention bit for bit.
@@ -98,12 +98,8 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
   }
   if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&list_bad, 1);
   __syncthreads();
-  if (list_bad) {                            // general lists: recomputed by the rescaling kernel
-    if (threadIdx.x < 2 && (threadIdx.x == 0 || has_b))
-      mark_block<OUT_F32>(a.out, head + (size_t)(2 * p + threadIdx.x) * S * D);
-    return;
-  }
-  if (w == 0) {                              // compaction in block order, 64 words per step
+  const bool general = list_bad != 0;        // uniform
+  if (w == 0 && !general) {                  // compaction in block order, 64 words per step
     int base = 0;
     for (int w0 = 0; w0 < words; w0 += 64) {
       const int wd = w0 + lane;
@@ -129,7 +125,7 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
     if (lane == 0) n_union = base;
   }
   __syncthreads();
-  const int U = n_union;
+  const int U = general ? 0 : n_union;
   auto ent = [&](int e) -> int {             // union entry e (block 0, kept by neither, past the end)
     return __builtin_amdgcn_readfirstlane(e < U ? (int)ulist[e] : 0);
   };
@@ -246,9 +242,19 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
   const bool over = overflowed16<D>(l_tot, oacc);
   if (__builtin_amdgcn_ballot_w64(over) != 0 && lane == 0) atomicOr(&wg_bad, 1);
   __syncthreads();
-  if (wg_bad) {
-    if (threadIdx.x < 2 && (threadIdx.x == 0 || has_b))
-      mark_block<OUT_F32>(a.out, head + (size_t)(2 * p + threadIdx.x) * S * D);
+  if (general || wg_bad) {
+#pragma unroll 1
+    for (int s = 0; s < (has_b ? 2 : 1); ++s) {
+      const int row = row0 + s;
+      const int32_t* idx = a.kv_idx + (size_t)row * a.kmax;
+      general_walk16<D, S, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase,
+                                    min(max(a.kv_count[row], 0), a.kmax),
+                                    [&](int t) {
+                                      const int b = __builtin_amdgcn_readfirstlane(idx[t]);
+                                      return b >= 0 && b < nB ? b : -1;
+                                    },
+                                    s == qsel);
+    }
     return;
   }
   const bool has[2] = {ref_set && l_tot[0] > 0.0f, ref_set && l_tot[1] > 0.0f};

@@ -24,8 +24,8 @@
 // After each kept block a query whose sum has passed 2^64 moves its reference
 // up by a power of two (O and l scaled exactly).  A block with a query that
 // still overflows (its logits jump by more than ~2^63 over the running sum
-// inside one block) is marked (NaN first element) and recomputed by the
-// per-iteration rescaling kernel that runs next.
+// inside one block) is walked again by the same workgroup with a running
+// maximum (general_walk16).
 //
 // Workgroup order: sparse lists run, inside a head, in frame tiles of 4
 // consecutive query blocks x 8 frames (frame_tile_order), so the query blocks
@@ -259,7 +259,8 @@ void attn_q16_kernel(AttnArgs a) {
   if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&wg_bad, 1);
   __syncthreads();
   if (wg_bad) {
-    if (threadIdx.x == 0 && i * S < N) mark_block<OUT_F32>(a.out, head + (size_t)i * S * D);
+    general_walk16<D, S, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase, count,
+                                  [&](int t) { const int b = raw_at(t); return in_range(b) ? b : -1; }, true);
     return;
   }
   const bool has[2] = {count > 0 && l_tot[0] > 0.0f, count > 0 && l_tot[1] > 0.0f};

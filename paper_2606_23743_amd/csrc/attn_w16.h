@@ -179,7 +179,7 @@ __device__ __forceinline__ void pv16(const bf16x8 (&pop)[QT], const unsigned cha
 // reference up by the sum's binary exponent and scales its O and l by the same
 // power of two (exact).  Rows never come near 2^64 in practice, so this is one
 // compare and a branch per block; a row that still overflows inside one block
-// is caught by overflowed16 at the end.
+// is caught by overflowed16 at the end and walked again (general_walk16).
 template <int D, int QT>
 __device__ __forceinline__ void rescale_if_large16(float (&l_part)[QT], float (&m_ref)[QT],
                                                    f32x4 (&oacc)[Geo16<D>::DT][QT]) {
@@ -219,7 +219,7 @@ __device__ __forceinline__ bool overflowed16(const float (&l_tot)[QT], const f32
   return bad;
 }
 
-// O = O^T / l of the lane's two queries (qbase + qt*16 + i, those below N) at
+// O = O^T / l of the lane's queries (qbase + qt*16 + i, those below N) at
 // d = 16dt + 4g .. +4, and their LSE; zeros and -inf for a query that attended
 // to nothing (has[qt] false)
 template <int D, bool OUT_F32, int QT>
@@ -248,6 +248,80 @@ __device__ __forceinline__ void store_query16(void* out, float* lse, size_t head
     }
     if (lse && g == 0)
       lse[lse_head + q] = has[qt] ? (m_ref[qt] + __log2f(l_tot[qt])) * 0.69314718055994530942f : -INFINITY;
+  }
+}
+
+// The general form of a query block, for a block whose fixed reference
+// overflowed (or, in the pair kernel, whose lists are not the selection
+// kernel's): the running maximum moves at every key block (online softmax), so
+// no sum can overflow.  Entered by every wave of the workgroup; `mine` is false
+// for waves that only load (the pair kernel's other block).  qbase: the wave's
+// first query; block_at(t): the t-th list entry, negative where it is skipped.
+// 16 queries at a time, so that it needs fewer registers than the fast loop
+// around it; one chunk at a time through stage 0, K twice (the block's maximum,
+// then its probabilities).  Several times slower than the fast loop, on rows
+// that real inputs do not have.
+template <int D, int S, bool OUT_F32, class Loader, class BlockAt>
+__device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& ld, const unsigned char* ks,
+                                               const unsigned char* vs, const int (&koff)[Geo16<D>::KS],
+                                               const int (&voff)[Geo16<D>::DT], int bh, int qbase, int count,
+                                               BlockAt block_at, bool mine) {
+  const int N = a.N, lane = ld.lane;
+  const size_t head = (size_t)bh * N * D;
+#pragma unroll 1
+  for (int half = 0; half < 2; ++half) {
+    bf16x8 qop[1][Geo16<D>::KS];
+    load_q16<D>(qop, a.q + head, qbase + half * 16, mine ? N : 0, lane);
+    float m_run[1] = {-INFINITY}, l_part[1] = {0.0f};
+    f32x4 oacc[Geo16<D>::DT][1];
+#pragma unroll
+    for (int dt = 0; dt < Geo16<D>::DT; ++dt) oacc[dt][0] = f32x4{};
+#pragma unroll 1
+    for (int t = 0; t < count; ++t) {
+      const int j = block_at(t);
+      if (j < 0) continue;
+      const int end = min(N, j * S + S);
+      float mx = -INFINITY;
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll 1
+        for (int key0 = j * S; key0 < end; key0 += 32) {
+          wait_vmcnt_lds_idle<0>();
+          wg_barrier();                      // every wave is done with the stage
+          load_tile<true>(ld, 0, key0);
+          load_tile<false>(ld, 0, key0);
+          wait_vmcnt<0>();
+          wg_barrier();
+          f32x4 s[2][1];
+          qk16<D>(s, ks, koff, qop);
+          if (N - key0 < 32) mask_tail16(s, N - key0, lane);
+          if (pass == 0) {
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[k2][0][r]);
+          } else {
+            bf16x8 pop[1];
+            softmax16(s, pop, l_part, m_run, a.scale_log2);
+            pv16<D>(pop, vs, voff, oacc);
+          }
+        }
+        if (pass == 0) {
+          const float m_new = fmaxf(m_run[0], quad_max(mx) * a.scale_log2);
+          const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
+          m_run[0] = m_new;
+          l_part[0] *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < Geo16<D>::DT; ++dt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) oacc[dt][0][r] *= alpha;
+        }
+      }
+    }
+    const float l_tot[1] = {quad_sum(l_part[0])};
+    const bool has[1] = {l_tot[0] > 0.0f};
+    store_query16<D, OUT_F32>(a.out, a.lse, head, (size_t)bh * N, qbase + half * 16, mine ? N : 0, oacc, l_tot, m_run,
+                              has, lane);
   }
 }
 

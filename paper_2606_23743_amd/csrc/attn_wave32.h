@@ -1,6 +1,5 @@
 // Building blocks of the bf16 attention kernels: the direct global -> LDS
-// chunk loads every kernel uses, the NaN mark of a block left to the
-// recompute pass, and the operand reads of the 32x32x16 form (per-lane LDS
+// chunk loads every kernel uses and the operand reads of the 32x32x16 form (per-lane LDS
 // offsets of the K operand and of the V transpose reads) that the
 // remainder's moment, weight and GEMM kernels (remainder.hip) use.  The
 // attention kernels' own arithmetic is the 16x16 form (attn_w16.h).
@@ -137,13 +136,6 @@ __device__ __forceinline__ bf16x8 tr_operand(const unsigned char* tile, int voff
   const u32x2 hw = __builtin_bit_cast(u32x2, hi);
   const u32x4 vw = {lw[0], lw[1], hw[0], hw[1]};
   return __builtin_bit_cast(bf16x8, vw);
-}
-
-// the NaN mark on a query block's first output element (recomputed later)
-template <bool OUT_F32>
-__device__ __forceinline__ void mark_block(void* out, size_t first) {
-  if constexpr (OUT_F32) static_cast<float*>(out)[first] = __builtin_nanf("");
-  else static_cast<uint16_t*>(out)[first] = 0x7FC0;
 }
 
 }  // namespace attn

@@ -26,9 +26,6 @@ struct SelectRule {
   int n_forced; // mass: forced first-frame blocks 0 .. n_forced-1
 };
 
-// The rescaling (per-iteration online softmax) kernel; attention.hip.
-hipError_t launch_attention_rescaling(const Dims& d, bool sparse, const AttnArgs& a, hipStream_t stream);
-
 // 32-queries-per-wave, two-waves-per-SIMD attention with a fixed reference max
 // on 16x16x32 products; attention_q16.hip.
 hipError_t launch_attention_q16(const Dims& d, bool sparse, const AttnArgs& a, hipStream_t stream);
