@@ -13,6 +13,7 @@ namespace sva {
 struct Dims {
   int B, H, N, D, S, nB;
   int frame_tokens;   // grid_h * grid_w
+  int call_pairs;     // B * H of the whole call, which a pass over some of its (b, h) pairs keeps
   double scale;       // softmax scale c (resolved, > 0)
   bool out_f32;
 };
@@ -36,6 +37,12 @@ hipError_t launch_attention_q16(const Dims& d, bool sparse, const AttnArgs& a, h
 // least 15% of the blocks).
 bool pair_attention_fits(const Dims& d, int kmax);
 hipError_t launch_attention_pair(const Dims& d, const AttnArgs& a, hipStream_t stream);
+
+// Attention for calls with few query blocks: 64-query tiles whose keys are
+// divided among `groups` (2 or 4) groups of waves of a workgroup;
+// attention_split.hip.  Sparse rows of at most kSplitMaxList entries.
+constexpr int kSplitMaxList = 2048;
+hipError_t launch_attention_split(const Dims& d, int groups, bool sparse, const AttnArgs& a, hipStream_t stream);
 
 // fp8 (e4m3) quantisation and attention; fp8_quant.hip, attention_fp8.hip.
 // Codes: q8, k8 [B, H, Np, D]; v8 [B, H, Np/64, D, 64] (Np = nB * S, padding
