@@ -272,14 +272,21 @@ hipError_t launch_pair(const Dims& d, const AttnArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-// Pairs pay off when neighbours share enough of their blocks, which goes with
-// denser lists.  Measured at D = 128 on the block-64 layers: rows of 18-100%
-// of the blocks ran 6-33% faster in pairs, 12% ran 2.5% slower and 10% 8%
-// slower (the waves of a block that does not keep an entry sit idle while it
-// is staged).  At D = 112 (the 2B-class layer) the single-block kernel already
-// runs near the dense rate and pairs were level or slower at every density.
+// A pair stages each entry of the union once for two query blocks, at the price
+// of waves that sit idle while an entry of the other block is worked on.  That
+// pays where the single-block kernel is held by the bytes that miss the L2s
+// (about 6.3 of the 6.7 TB/s the fabric gives), which takes long rows of long
+// sequences: time of pairs over single blocks, by kmax * nB: 1.13-1.46 up to
+// 15,000 (N = 12,000), 1.14-1.25 at 42,000, 1.06-1.18 at 105,000 (N = 32,760),
+// 1.05 at 157,000, 1.02 at 225,000, 1.01-1.02 at 245,000 (N = 63,240 and 75,600),
+// 0.89-0.95 at 392,000, 0.87 at 350,000 (N = 75,600), 0.77 at 559,000, and on
+// mass lists with the first frame forced 0.986 at 166,000 (N = 46,662).  Rows of
+// under 15% of the blocks share too few with their neighbour (10% ran 8%
+// slower at N = 75,600).  At D = 112 pairs were level or slower at every
+// density.
 bool pair_attention_fits(const Dims& d, int kmax) {
-  return d.S == 64 && d.D == 128 && d.nB <= kPairMaxBlocks && 20LL * kmax >= 3LL * d.nB;
+  return d.S == 64 && d.D == 128 && d.nB <= kPairMaxBlocks && 20LL * kmax >= 3LL * d.nB &&
+         (int64_t)kmax * d.nB >= 160000;
 }
 
 hipError_t launch_attention_pair(const Dims& d, const AttnArgs& a, hipStream_t stream) {
