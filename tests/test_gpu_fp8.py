@@ -234,6 +234,20 @@ def test_fp8_quantise_and_attend(name, B, H, D, grid, S, keep):
                 f"rms {rms_u:.2e} (model {pred_u:.2e})")
 
 
+@pytest.mark.parametrize("D,S", [(64, 64), (112, 128), (128, 64)])
+@pytest.mark.parametrize("n", [1, 255, 257, 321, 16 * 256 + 17])
+def test_fp8_quantiser_segments(n, D, S):
+    # the statistics' segments (256 tokens, four rows in flight per lane) and the
+    # runs of segments that are added side by side, at their edges
+    wl = workloads.small_case(f"seg{n}", 1, 2, D, (1, 1, n), S, "topk", keep_ratio=1.0, seed=n)
+    say(f"[fp8 segments n={n} D={D} S={S}]")
+    bits = inputs.generate(wl)
+    dev = device_inputs(bits)
+    quant = sva.quantize_fp8(sva.problem_for(wl), dev["q"], dev["k"], dev["v"])
+    torch.cuda.synchronize()
+    _check_quant(wl, bits, quant)
+
+
 @pytest.mark.parametrize("S,D,step", [(128, 128, 3.0), (128, 128, 40.0), (64, 128, 3.0), (64, 112, 40.0),
                                       (128, 64, -3.0)])
 def test_fp8_guard_rescales_with_rising_logits(S, D, step):
