@@ -5,10 +5,10 @@
 //   score  s[b, n] = sum_c x[b, n, c]^2 in float64 (the products of bf16 values
 //          are exact there); one wave per token, 16-byte loads.
 //   select the k largest scores of each batch entry (ties to the lower token
-//          index), listed in ascending order: a grid-wide radix select over
-//          the scores' order keys finds the k-th largest key, then a counting
-//          pass and a write pass over token segments emit kept_idx (ascending)
-//          and kept_pos (the position of each kept token, -1 for the others).
+//          index), listed in ascending order: two grid-wide passes over the
+//          scores' order keys find the k-th largest key, then a write pass over
+//          token segments emits kept_idx (ascending) and kept_pos (the position
+//          of each kept token, -1 for the others).
 //   gather x_kept[b, j] = x[b, kept_idx[b, j]]; scatter out[b, n] = y_kept[b,
 //          kept_pos[b, n]] for kept tokens and base[b, n] for the others.  One
 //          wave per row, 16-byte loads and stores.
@@ -34,23 +34,32 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// ---- selection: a radix select over the 64-bit order keys, grid-wide ----
+// ---- selection of the k-th largest order key, grid-wide ----
 //
-// Digits of 12 bits from the top (bits 63..52, 51..40, ..., 3..0): each pass
-// histograms the digit of every key that matches the prefix resolved so far
-// (an LDS histogram per workgroup, flushed to the batch entry's global one);
-// the last workgroup to finish the pass (a ticket counter, no waiting) picks
-// the digit holding the k-th largest key and clears the histogram for the next
-// pass.  The search ends when every key with the resolved prefix is needed
-// (then the prefix with zero low bits is the threshold) or all 64 bits are
-// resolved; later passes return at once.  Then a counting pass finds, per
-// token segment, the keys above the threshold and equal to it, the last
-// workgroup turns those counts into output offsets and tie quotas, and the
-// write pass emits kept_idx and kept_pos in token order.
+// Two passes over the scores instead of one per digit, because what such a pass
+// costs is not its reads (0.5 MB at 63,240 tokens) but its launch and the
+// hand-off to the last workgroup, 11-12 us together:
+//   bracket  every wave ranks the same 64 evenly spaced keys and takes a bracket
+//            that holds the k-th largest with 4 standard deviations to spare;
+//            the keys inside fall into 4094 equal bins (an LDS histogram per
+//            workgroup, flushed to the batch entry's), those above are counted;
+//            the last workgroup to finish (a ticket counter, no waiting) picks
+//            the bin of the k-th largest key.
+//   resolve  per token segment: the keys above that bin and in it, the latter
+//            also listed (a few dozen of 63,240 tokens); the last workgroup
+//            finds the threshold among them and turns the counts into output
+//            offsets and tie quotas.
+// The rest is for scores that defeat the bracket (it missed, or one bin holds
+// more than kCand keys): a bin of one repeated key is its threshold as it
+// stands; otherwise the last workgroup runs a radix select over all keys by
+// itself.  Then the write pass emits kept_idx and kept_pos in token order.
+// Select of 63,240 tokens, everything after the scores: 90 us with six digit
+// passes and a counting pass, 38 us now.
 
 constexpr int kDigitBits = 12;
 constexpr int kBins = 1 << kDigitBits;
-constexpr int kPasses = 6;                       // ceil(64 / 12)
+constexpr int kCand = kBins;                     // listed keys, in the histogram's place
+constexpr int kRank = 512;                       // of which this many are ranked against each other
 constexpr int kSegThreads = 512;
 constexpr int kMaxSegs = 1024;
 // tokens per segment (one workgroup each): fewer, larger segments cut the
@@ -58,13 +67,14 @@ constexpr int kMaxSegs = 1024;
 // ticket atomic); 2048 measured fastest at 111600 tokens
 constexpr int kSegTokens = 2048;
 
-struct SelState {            // per batch entry, at the head of its workspace slice
-  unsigned long long prefix; // the resolved high bits of the k-th largest key
-  int need;                  // keys still to take among those matching the prefix
-  int done;                  // the threshold is resolved
-  unsigned int ticket;       // workgroups finished in the current pass
-  int need_eq;               // keys equal to the threshold that are kept
-  int pad[2];
+struct SelState {                // per batch entry, at the head of its workspace slice
+  unsigned long long threshold;  // the k-th largest key
+  unsigned long long lo, hi;     // its bin, inclusive
+  unsigned long long kmin, kmax; // smallest and largest key in the bin
+  int need;                      // keys of the bin that are kept
+  unsigned int cand;             // keys in the bin
+  unsigned int ticket;           // workgroups finished in the current pass
+  int need_eq;                   // keys equal to the threshold that are kept
 };
 
 static_assert(sizeof(SelState) + sizeof(uint32_t) * kBins + 4 * sizeof(int) * kMaxSegs <=
@@ -72,7 +82,7 @@ static_assert(sizeof(SelState) + sizeof(uint32_t) * kBins + 4 * sizeof(int) * kM
 
 struct SelWs {
   SelState* st;
-  uint32_t* hist;            // [kBins]
+  uint32_t* hist;            // [kBins], then the token indices of the bin's keys
   int* gt;                   // [kMaxSegs] per segment: keys above the threshold
   int* eq;                   // [kMaxSegs] per segment: keys equal to it
   int* kept_before;          // [kMaxSegs] exclusive offsets into kept_idx
@@ -115,20 +125,36 @@ __device__ int block_scan(int v, int* red, int& total) {
   return before + incl - v;
 }
 
-// scores: one wave per token; blocks below B also initialise the selection state
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+// Sixteen bytes, non-temporal (NT) where the tensor is too large for the caches to
+// keep anything of it for the next reader: such traffic then leaves in the 256 MB
+// memory-side cache what a later kernel does read again.
+template <bool NT>
+__device__ __forceinline__ u32x4 load16(const uint16_t* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return *reinterpret_cast<const u32x4*>(p);
+}
+template <bool NT>
+__device__ __forceinline__ void store16(uint16_t* p, u32x4 v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p));
+  else *reinterpret_cast<u32x4*>(p) = v;
+}
+
+// scores: one wave per token, four 16-byte loads in flight per lane; blocks below
+// B also initialise the selection state
 __global__ __launch_bounds__(256) void token_score_kernel(const uint16_t* __restrict__ x,
                                                           double* __restrict__ scores,
                                                           unsigned char* __restrict__ ws, int B,
-                                                          int rows, int C, int k) {
+                                                          int rows, int C) {
   if (blockIdx.x < (unsigned)B) {
     const SelWs w = sel_ws(ws, blockIdx.x);
     for (int i = threadIdx.x; i < kBins; i += 256) w.hist[i] = 0;
     if (threadIdx.x == 0) {
-      w.st->prefix = 0;
-      w.st->need = k;
-      w.st->done = 0;
+      w.st->kmin = ~0ull;
+      w.st->kmax = 0;
+      w.st->cand = 0;
       w.st->ticket = 0;
-      w.st->need_eq = 0;
     }
   }
   const int lane = threadIdx.x & 63;
@@ -136,12 +162,20 @@ __global__ __launch_bounds__(256) void token_score_kernel(const uint16_t* __rest
   if (row >= rows) return;
   const uint16_t* p = x + (size_t)row * C;
   double acc = 0.0;
-  for (int c = lane * 8; c < C; c += 512) {
-    const uint4 q = *reinterpret_cast<const uint4*>(p + c);
-    const float v[8] = {lo16(q.x), hi16(q.x), lo16(q.y), hi16(q.y), lo16(q.z), hi16(q.z), lo16(q.w), hi16(q.w)};
+  auto add = [&](u32x4 q) {
+    const float v[8] = {lo16(q[0]), hi16(q[0]), lo16(q[1]), hi16(q[1]), lo16(q[2]), hi16(q[2]), lo16(q[3]), hi16(q[3])};
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc = fma((double)v[e], (double)v[e], acc);
+  };
+  int c = lane * 8;
+  for (; c + 3 * 512 < C; c += 4 * 512) {
+    u32x4 q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = load16<false>(p + c + u * 512);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) add(q[u]);
   }
+  for (; c < C; c += 512) add(load16<false>(p + c));
   acc = wave_sum(acc);
   if (lane == 0) scores[row] = acc;
 }
@@ -157,94 +191,209 @@ __device__ bool last_to_finish(unsigned int* ticket, int* flag) {
   return last;
 }
 
-// one digit of the radix select; grid (segments, B)
-__global__ __launch_bounds__(kSegThreads) void token_pass_kernel(const double* __restrict__ scores,
-                                                                 unsigned char* __restrict__ ws,
-                                                                 int N, int seg_len, int pass) {
-  __shared__ uint32_t h[kBins];
-  __shared__ int red[kSegThreads / 64];
-  __shared__ int flag;
-  __shared__ int pick[3];
-  const int b = blockIdx.y;
-  const SelWs w = sel_ws(ws, b);
-  if (w.st->done) return;                                   // uniform
-  const int hi = 63 - kDigitBits * pass;
-  const int lo = hi - kDigitBits + 1 > 0 ? hi - kDigitBits + 1 : 0;
-  const uint64_t mask = (1ull << (hi - lo + 1)) - 1;
-  const uint64_t prefix = w.st->prefix;
-  for (int i = threadIdx.x; i < kBins; i += kSegThreads) h[i] = 0;
-  __syncthreads();
-  const double* s = scores + (size_t)b * N;
-  const int n0 = blockIdx.x * seg_len, n1 = min(N, n0 + seg_len);
-  for (int n = n0 + threadIdx.x; n < n1; n += kSegThreads) {
-    const uint64_t key = order_key(s[n]);
-    if (hi == 63 || (key >> (hi + 1)) == (prefix >> (hi + 1)))
-      atomicAdd(&h[(key >> lo) & mask], 1u);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < kBins; i += kSegThreads)
-    if (h[i]) atomicAdd(&w.hist[i], h[i]);
-  if (!last_to_finish(&w.st->ticket, &flag)) return;
+// the value that the wave's lane `src` holds
+__device__ __forceinline__ uint64_t lane_key(uint64_t v, int src) {
+  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, src), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), src);
+  return (uint64_t)hi << 32 | lo;
+}
 
-  // the last workgroup: bins from the top until the k-th largest key is reached
-  constexpr int BPT = kBins / kSegThreads;                  // bins per thread
-  const int t0 = threadIdx.x * BPT;
-  uint32_t mine[BPT];
+// The bracket [lo, hi] of the k-th largest of n keys from 64 evenly spaced ones
+// (each wave by itself; the same everywhere).  The rank of the threshold among
+// the 64 has standard deviation 8 sqrt(p (1 - p)), p = k / n; past the ends of
+// the sample the bracket goes on for the sample's own range.
+__device__ void sample_bracket(const double* s, int n, int k, uint64_t& lo, uint64_t& hi) {
+  const int lane = threadIdx.x & 63;
+  const uint64_t key = order_key(s[(int)((int64_t)lane * n >> 6)]);
+  int pos = 0;                                              // place in descending order
+#pragma unroll 8
+  for (int j = 0; j < 64; ++j) {
+    const uint64_t o = lane_key(key, j);
+    pos += (o > key || (o == key && j < lane)) ? 1 : 0;
+  }
+  auto at = [&](int i) { return lane_key(key, __builtin_ctzll(__builtin_amdgcn_ballot_w64(pos == i))); };
+  const float p = (float)k / (float)n;
+  const float mid = 64.0f * p, margin = 32.0f * sqrtf(fmaxf(p * (1.0f - p), 0.0f)) + 1.0f;
+  const int ih = __builtin_amdgcn_readfirstlane((int)floorf(mid - margin));
+  const int il = __builtin_amdgcn_readfirstlane((int)ceilf(mid + margin));
+  const uint64_t first = at(0), last = at(63), range = first - last;
+  hi = ih >= 0 ? at(min(ih, 63)) : (first + range < first ? ~0ull : first + range);
+  lo = il <= 63 ? at(max(il, 0)) : (last < range ? 0 : last - range);
+}
+
+// the bin (from the top) that holds the need-th largest of the counted keys: pick
+// = {bin, keys above it, keys in it}, or bin -1.  Every thread passes its own
+// kBins / kSegThreads counts, in bin order.
+__device__ void pick_bin(const uint32_t (&mine)[kBins / kSegThreads], int need, int* red, int (&pick)[3]) {
+  constexpr int BPT = kBins / kSegThreads;
   int sum = 0;
 #pragma unroll
-  for (int e = 0; e < BPT; ++e) {
-    mine[e] = __hip_atomic_load(&w.hist[t0 + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    sum += (int)mine[e];
-  }
+  for (int e = 0; e < BPT; ++e) sum += (int)mine[e];
+  if (threadIdx.x == 0) pick[0] = -1;
   int total;
-  const int excl = block_scan(sum, red, total);
+  const int excl = block_scan(sum, red, total);             // (two barriers)
   int above = total - excl - sum;                           // keys in higher bins
-  const int need = w.st->need;
 #pragma unroll
   for (int e = BPT - 1; e >= 0; --e) {
     const int c = (int)mine[e];
     if (above < need && need <= above + c) {
-      pick[0] = t0 + e;
+      pick[0] = threadIdx.x * BPT + e;
       pick[1] = above;
       pick[2] = c;
     }
     above += c;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kBins; i += kSegThreads) w.hist[i] = 0;
+}
+
+// grid (segments, B)
+__global__ __launch_bounds__(kSegThreads) void token_bracket_kernel(const double* __restrict__ scores,
+                                                                    unsigned char* __restrict__ ws,
+                                                                    int N, int seg_len, int k) {
+  __shared__ uint32_t h[kBins];
+  __shared__ int red[kSegThreads / 64];
+  __shared__ int flag;
+  __shared__ int pick[3];
+  const int b = blockIdx.y;
+  const SelWs w = sel_ws(ws, b);
+  for (int i = threadIdx.x; i < kBins; i += kSegThreads) h[i] = 0;
+  const double* s = scores + (size_t)b * N;
+  uint64_t lo, hi;
+  sample_bracket(s, N, k, lo, hi);
+  // bins 1 .. kBins - 2 cover [lo, hi]; the top bin takes what is above
+  const int bits = hi > lo ? 64 - __builtin_clzll(hi - lo) : 0;
+  int shift = max(0, bits - kDigitBits);
+  if (((hi - lo) >> shift) > kBins - 3) ++shift;
+  __syncthreads();
+  const int n0 = blockIdx.x * seg_len, n1 = min(N, n0 + seg_len);
+  int above = 0;
+  for (int n = n0 + threadIdx.x; n < n1; n += kSegThreads) {
+    const uint64_t key = order_key(s[n]);
+    if (key > hi) ++above;
+    else if (key >= lo) atomicAdd(&h[1 + (int)((key - lo) >> shift)], 1u);
+  }
+  int all_above;
+  block_scan(above, red, all_above);                        // (the barriers also close the histogram)
+  if (threadIdx.x == 0) h[kBins - 1] = (uint32_t)all_above;
+  __syncthreads();
+  for (int i = threadIdx.x; i < kBins; i += kSegThreads)
+    if (h[i]) atomicAdd(&w.hist[i], h[i]);
+  if (!last_to_finish(&w.st->ticket, &flag)) return;
+
+  constexpr int BPT = kBins / kSegThreads;                  // bins per thread
+  uint32_t mine[BPT];
+#pragma unroll
+  for (int e = 0; e < BPT; ++e)
+    mine[e] = __hip_atomic_load(&w.hist[threadIdx.x * BPT + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  pick_bin(mine, k, red, pick);
   if (threadIdx.x == 0) {
-    const int left = need - pick[1];
-    w.st->prefix = prefix | ((uint64_t)pick[0] << lo);
-    w.st->need = left;
-    w.st->done = (left == pick[2] || lo == 0) ? 1 : 0;
+    uint64_t blo, bhi;
+    int need;
+    if (pick[0] == kBins - 1) {                             // above the bracket
+      blo = hi + 1;
+      bhi = ~0ull;
+      need = k;
+    } else if (pick[0] > 0) {
+      blo = lo + ((uint64_t)(pick[0] - 1) << shift);
+      bhi = min(hi, blo + ((1ull << shift) - 1));
+      need = k - pick[1];
+    } else {                                                // below it: fewer than k keys were counted
+      blo = 0;
+      bhi = lo - 1;
+      need = -1;                                            // known once the keys above are counted
+    }
+    w.st->lo = blo;
+    w.st->hi = bhi;
+    w.st->need = need;
     w.st->ticket = 0;
   }
 }
 
-// keys above and equal to the threshold per segment; the last workgroup turns
-// them into output offsets and tie quotas.  grid (segments, B)
-__global__ __launch_bounds__(kSegThreads) void token_count_kernel(const double* __restrict__ scores,
-                                                                  unsigned char* __restrict__ ws,
-                                                                  int N, int seg_len, int k) {
+// The need-th largest of the keys in [lo, hi] among key_at(0 .. count-1), by one
+// workgroup: digits of 12 bits from the highest in which lo and hi differ.
+template <class KeyAt>
+__device__ uint64_t radix_pick(int count, KeyAt key_at, uint64_t lo, uint64_t hi, int need, uint32_t* h, int* red,
+                               int (&pick)[3]) {
+  int top = lo == hi ? 0 : 64 - __builtin_clzll(lo ^ hi);   // bits below `top` are open
+  uint64_t prefix = lo;
+  while (top > 0) {
+    const int width = min(kDigitBits, top), low = top - width;
+    for (int i = threadIdx.x; i < kBins; i += kSegThreads) h[i] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < count; i += kSegThreads) {
+      const uint64_t key = key_at(i);
+      if (key >= lo && key <= hi && (top == 64 || (key >> top) == (prefix >> top)))
+        atomicAdd(&h[(key >> low) & ((1ull << width) - 1)], 1u);
+    }
+    __syncthreads();
+    constexpr int BPT = kBins / kSegThreads;
+    uint32_t mine[BPT];
+#pragma unroll
+    for (int e = 0; e < BPT; ++e) mine[e] = h[threadIdx.x * BPT + e];
+    pick_bin(mine, need, red, pick);
+    prefix = (((prefix >> low) & ~((1ull << width) - 1)) | (uint64_t)pick[0]) << low;
+    need -= pick[1];
+    top = low;
+    __syncthreads();                                        // pick and h are reused
+  }
+  return prefix;
+}
+
+// grid (segments, B)
+__global__ __launch_bounds__(kSegThreads) void token_resolve_kernel(const double* __restrict__ scores,
+                                                                    unsigned char* __restrict__ ws,
+                                                                    int N, int seg_len, int k) {
+  __shared__ uint32_t h[kBins];                             // also: the candidates' keys
   __shared__ int red[kSegThreads / 64];
   __shared__ int flag;
-  const int b = blockIdx.y;
+  __shared__ int pick[3];
+  __shared__ unsigned long long thr, mm[2];
+  __shared__ int seg_gt[kMaxSegs], seg_eq[kMaxSegs];
+  const int b = blockIdx.y, lane = threadIdx.x & 63;
   const SelWs w = sel_ws(ws, b);
-  const uint64_t T = w.st->prefix;
+  const uint64_t lo = w.st->lo, hi = w.st->hi;
+  int* list = reinterpret_cast<int*>(w.hist);
   const double* s = scores + (size_t)b * N;
   const int n0 = blockIdx.x * seg_len, n1 = min(N, n0 + seg_len);
-  int gt = 0, eq = 0;
-  for (int n = n0 + threadIdx.x; n < n1; n += kSegThreads) {
-    const uint64_t key = order_key(s[n]);
-    gt += key > T ? 1 : 0;
-    eq += key == T ? 1 : 0;
+  if (threadIdx.x == 0) {
+    mm[0] = ~0ull;
+    mm[1] = 0;
   }
-  int tg, te;
+  __syncthreads();
+  int gt = 0, in = 0;
+  uint64_t kmin = ~0ull, kmax = 0;
+  for (int base = n0; base < n1; base += kSegThreads) {     // uniform trip count
+    const int n = base + threadIdx.x;
+    const uint64_t key = n < n1 ? order_key(s[n]) : 0;
+    const bool here = n < n1 && key >= lo && key <= hi;
+    gt += n < n1 && key > hi ? 1 : 0;
+    const uint64_t m = __builtin_amdgcn_ballot_w64(here);
+    if (m != 0) {                                           // one atomic per wave
+      unsigned at = 0;
+      if (lane == 0) at = atomicAdd(&w.st->cand, (unsigned)__builtin_popcountll(m));
+      at = __builtin_amdgcn_readfirstlane(at) + (unsigned)__builtin_popcountll(m & ((1ull << lane) - 1));
+      if (here) {
+        ++in;
+        kmin = min(kmin, key);
+        kmax = max(kmax, key);
+        if (at < kCand) list[at] = n;
+      }
+    }
+  }
+  int tg, ti;
   block_scan(gt, red, tg);
-  block_scan(eq, red, te);
+  block_scan(in, red, ti);
+  if (in != 0) {
+    atomicMin(&mm[0], (unsigned long long)kmin);
+    atomicMax(&mm[1], (unsigned long long)kmax);
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
     w.gt[blockIdx.x] = tg;
-    w.eq[blockIdx.x] = te;
+    w.eq[blockIdx.x] = ti;
+    if (ti != 0) {
+      atomicMin(&w.st->kmin, mm[0]);
+      atomicMax(&w.st->kmax, mm[1]);
+    }
   }
   if (!last_to_finish(&w.st->ticket, &flag)) return;
 
@@ -256,10 +405,84 @@ __global__ __launch_bounds__(kSegThreads) void token_count_kernel(const double* 
     const int sgi = threadIdx.x * SPT + i;
     g[i] = sgi < nseg ? __hip_atomic_load(&w.gt[sgi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     e[i] = sgi < nseg ? __hip_atomic_load(&w.eq[sgi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    seg_gt[sgi] = seg_eq[sgi] = 0;
+    sg += g[i];
+  }
+  int all_gt;
+  block_scan(sg, red, all_gt);
+  const int count = (int)__hip_atomic_load(&w.st->cand, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t first = __hip_atomic_load(&w.st->kmin, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t last = __hip_atomic_load(&w.st->kmax, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int need = k - all_gt;                              // 1 .. count
+  auto cand_at = [&](int i) { return __hip_atomic_load(&list[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  uint64_t T;
+  if (first == last) {                                      // one key, however often: counts as they stand
+    T = first;
+  } else if (count <= kCand) {
+    if (count <= kRank) {
+      uint64_t* keys = reinterpret_cast<uint64_t*>(h);
+      uint64_t key = 0;
+      if ((int)threadIdx.x < count) keys[threadIdx.x] = key = order_key(s[cand_at(threadIdx.x)]);
+      __syncthreads();
+      if ((int)threadIdx.x < count) {
+        int n_gt = 0, n_ge = 0;
+        for (int i = 0; i < count; ++i) {
+          n_gt += keys[i] > key ? 1 : 0;
+          n_ge += keys[i] >= key ? 1 : 0;
+        }
+        if (n_gt < need && need <= n_ge) thr = key;         // equal keys write the same value
+      }
+      __syncthreads();
+      T = thr;
+    } else {
+      T = radix_pick(count, [&](int i) { return order_key(s[cand_at(i)]); }, first, last, need, h, red, pick);
+    }
+    for (int i = threadIdx.x; i < count; i += kSegThreads) {
+      const int n = cand_at(i);
+      const uint64_t key = order_key(s[n]);
+      if (key > T) atomicAdd(&seg_gt[n / seg_len], 1);
+      if (key == T) atomicAdd(&seg_eq[n / seg_len], 1);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) {
+      g[i] += seg_gt[threadIdx.x * SPT + i];
+      e[i] = seg_eq[threadIdx.x * SPT + i];
+    }
+  } else {
+    T = radix_pick(N, [&](int i) { return order_key(s[i]); }, first, last, need, h, red, pick);
+    for (int sgi = threadIdx.x >> 6; sgi < nseg; sgi += kSegThreads / 64) {
+      int n_gt = 0, n_eq = 0;
+      const int end = min(N, (sgi + 1) * seg_len);
+      for (int n = sgi * seg_len + lane; n < end; n += 64) {
+        const uint64_t key = order_key(s[n]);
+        n_gt += key > T ? 1 : 0;
+        n_eq += key == T ? 1 : 0;
+      }
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        n_gt += __shfl_xor(n_gt, off, 64);
+        n_eq += __shfl_xor(n_eq, off, 64);
+      }
+      if (lane == 0) {
+        seg_gt[sgi] = n_gt;
+        seg_eq[sgi] = n_eq;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < SPT; ++i) {
+      g[i] = seg_gt[threadIdx.x * SPT + i];
+      e[i] = seg_eq[threadIdx.x * SPT + i];
+    }
+  }
+  sg = 0;
+#pragma unroll
+  for (int i = 0; i < SPT; ++i) {
     sg += g[i];
     se += e[i];
   }
-  int all_gt, all_eq;
+  int all_eq;
   block_scan(sg, red, all_gt);
   int eb = block_scan(se, red, all_eq);
   const int need_eq = k - all_gt;                           // equal keys kept, lowest index first
@@ -284,8 +507,8 @@ __global__ __launch_bounds__(kSegThreads) void token_count_kernel(const double* 
     eb += e[i];
   }
   if (threadIdx.x == 0) {
+    w.st->threshold = T;
     w.st->need_eq = need_eq;
-    w.st->ticket = 0;
   }
 }
 
@@ -298,7 +521,7 @@ __global__ __launch_bounds__(kSegThreads) void token_write_kernel(const double* 
   __shared__ int red[kSegThreads / 64];
   const int b = blockIdx.y;
   const SelWs w = sel_ws(const_cast<unsigned char*>(ws), b);
-  const uint64_t T = w.st->prefix;
+  const uint64_t T = w.st->threshold;
   const int need_eq = w.st->need_eq;
   int pos = w.kept_before[blockIdx.x], ties = w.eq_before[blockIdx.x];
   const double* s = scores + (size_t)b * N;
@@ -323,7 +546,22 @@ __global__ __launch_bounds__(kSegThreads) void token_write_kernel(const double* 
   }
 }
 
+// one row by one wave, four loads in flight per lane
+template <bool NT>
+__device__ __forceinline__ void copy_row(uint16_t* dst, const uint16_t* src, int C, int lane) {
+  int c = lane * 8;
+  for (; c + 3 * 512 < C; c += 4 * 512) {
+    u32x4 q[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) q[u] = load16<NT>(src + c + u * 512);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) store16<NT>(dst + c + u * 512, q[u]);
+  }
+  for (; c < C; c += 512) store16<NT>(dst + c, load16<NT>(src + c));
+}
+
 // x_kept[b, j] = x[b, kept_idx[b, j]]; one wave per kept row
+template <bool NT>
 __global__ __launch_bounds__(256) void token_gather_kernel(const uint16_t* __restrict__ x,
                                                            const int32_t* __restrict__ kept_idx,
                                                            uint16_t* __restrict__ x_kept, int B,
@@ -339,11 +577,11 @@ __global__ __launch_bounds__(256) void token_gather_kernel(const uint16_t* __res
     return;
   }
   const uint16_t* src = x + ((size_t)b * N + n) * C;
-  for (int c = lane * 8; c < C; c += 512)
-    *reinterpret_cast<uint4*>(dst + c) = *reinterpret_cast<const uint4*>(src + c);
+  copy_row<NT>(dst, src, C, lane);
 }
 
 // out[b, n] = y_kept[b, kept_pos[b, n]] if kept, else base[b, n]; one wave per row
+template <bool NT>
 __global__ __launch_bounds__(256) void token_scatter_kernel(const uint16_t* __restrict__ y_kept,
                                                             const int32_t* __restrict__ kept_pos,
                                                             const uint16_t* __restrict__ base,
@@ -356,9 +594,15 @@ __global__ __launch_bounds__(256) void token_scatter_kernel(const uint16_t* __re
   const int pos = kept_pos[row];
   const uint16_t* src = (pos >= 0 && pos < k) ? y_kept + ((size_t)b * k + pos) * C : base + (size_t)row * C;
   uint16_t* dst = out + (size_t)row * C;
-  for (int c = lane * 8; c < C; c += 512)
-    *reinterpret_cast<uint4*>(dst + c) = *reinterpret_cast<const uint4*>(src + c);
+  copy_row<NT>(dst, src, C, lane);
 }
+
+// Gather and scatter of tensors past the caches stream (select, gather and scatter
+// together, us, plain / streaming): 33 MB 52.1 / 53.0, 131 MB 127.8 / 111.6,
+// 518 MB 423 / 354, 1.2 GB 960 / 840.  The scores' reads
+// do not: gather and scatter find the end of x in the cache (518 MB 356 / 372, 1.03
+// GB 704 / 721).
+bool streams_past_caches(int B, int N, int C) { return (int64_t)B * N * C * 2 >= (64 << 20); }
 
 }  // namespace
 
@@ -373,18 +617,14 @@ hipError_t launch_token_select(int B, int N, int C, int k, const uint16_t* x, do
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   const int rows = B * N;
   const int grid = max((rows + 3) / 4, B);
-  hipLaunchKernelGGL(token_score_kernel, dim3(grid), dim3(256), 0, stream, x, scores, ws, B, rows, C, k);
+  hipLaunchKernelGGL(token_score_kernel, dim3(grid), dim3(256), 0, stream, x, scores, ws, B, rows, C);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int nseg = token_select_segments(N);
   const int seg_len = (N + nseg - 1) / nseg;
-  for (int pass = 0; pass < kPasses; ++pass) {
-    hipLaunchKernelGGL(token_pass_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N,
-                       seg_len, pass);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(token_count_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N,
-                     seg_len, k);
+  hipLaunchKernelGGL(token_bracket_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N, seg_len, k);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(token_resolve_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N, seg_len, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(token_write_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws,
                      kept_idx, kept_pos, N, seg_len, k);
@@ -427,7 +667,11 @@ hipError_t token_select_scratch(hipStream_t stream, void** ptr) {
 hipError_t launch_token_gather(int B, int N, int C, int k, const uint16_t* x, const int32_t* kept_idx,
                                uint16_t* x_kept, hipStream_t stream) {
   const int rows = B * k;
-  hipLaunchKernelGGL(token_gather_kernel, dim3((rows + 3) / 4), dim3(256), 0, stream, x, kept_idx,
+  if (streams_past_caches(B, N, C))
+    hipLaunchKernelGGL(token_gather_kernel<true>, dim3((rows + 3) / 4), dim3(256), 0, stream, x, kept_idx,
+                     x_kept, B, N, C, k);
+  else
+    hipLaunchKernelGGL(token_gather_kernel<false>, dim3((rows + 3) / 4), dim3(256), 0, stream, x, kept_idx,
                      x_kept, B, N, C, k);
   return hipGetLastError();
 }
@@ -436,7 +680,11 @@ hipError_t launch_token_scatter(int B, int N, int C, int k, const uint16_t* y_ke
                                 const int32_t* kept_pos, const uint16_t* base, uint16_t* out,
                                 hipStream_t stream) {
   const int rows = B * N;
-  hipLaunchKernelGGL(token_scatter_kernel, dim3((rows + 3) / 4), dim3(256), 0, stream, y_kept,
+  if (streams_past_caches(B, N, C))
+    hipLaunchKernelGGL(token_scatter_kernel<true>, dim3((rows + 3) / 4), dim3(256), 0, stream, y_kept,
+                     kept_pos, base, out, B, N, C, k);
+  else
+    hipLaunchKernelGGL(token_scatter_kernel<false>, dim3((rows + 3) / 4), dim3(256), 0, stream, y_kept,
                      kept_pos, base, out, B, N, C, k);
   return hipGetLastError();
 }

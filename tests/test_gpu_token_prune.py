@@ -138,6 +138,37 @@ def test_ties_across_segments():
         assert _check_select(bits, r, scores, kept_idx, kept_pos) == 0, r
 
 
+@pytest.mark.parametrize("N,r,kind", [
+    (5000, 0.5, "cluster"),        # one bin holds 3000 different keys: the listed keys, digit by digit
+    (30000, 0.5, "cluster"),       # 18000 of them: more than the list holds, all keys by one workgroup
+    (30000, 0.59995, "cluster"),   # the cut just above the zero rows
+    (30000, 0.7, "cluster"),       # inside the zero rows
+    (30000, 3e-4, "outliers"),     # the cut above the sampled bracket
+    (30000, 0.9998, "outliers"),   # below it
+    (30000, 1.0, "outliers"),
+    (2048 * 3 + 1, 0.5, "plain"),  # a segment of one token more
+    (64, 0.5, "plain"), (65, 0.99, "plain"),
+])
+def test_select_score_distributions(N, r, kind):
+    C = 16
+    rng = np.random.default_rng(N)
+    x = np.zeros((2, N, C), dtype=np.float32)
+    if kind == "cluster":          # 40% zero rows, the others within 1% of one score
+        live = rng.permutation(N)[: N - 2 * N // 5]
+        x[:, live, 0] = 1.0
+        x[:, live, 1:] = rng.normal(size=(2, len(live), C - 1)) * 0.02
+    else:
+        x[:] = rng.normal(size=x.shape)
+        if kind == "outliers":
+            x[:, rng.permutation(N)[:20]] *= 2.0 ** 30
+            x[:, rng.permutation(N)[:20]] *= 2.0 ** -30
+    bits = (x.view(np.uint32) >> 16).astype(np.uint16)
+    say(f"[token_prune {kind} N={N} r={r}]")
+    scores, kept_idx, kept_pos = sva.token_select(_dev(bits), r)
+    torch.cuda.synchronize()
+    _check_select(bits, r, scores, kept_idx, kept_pos)
+
+
 def test_in_place_scatter_and_round_trip():
     """select -> gather -> scatter of the unchanged rows returns the input, in
     place over a copy of it as well."""
@@ -154,6 +185,23 @@ def test_in_place_scatter_and_round_trip():
     kp = kept_pos.cpu().numpy()
     zb = _bits(zero_base)
     assert np.array_equal(zb[kp >= 0], bits[kp >= 0]) and not zb[kp < 0].any()
+
+
+@pytest.mark.parametrize("N,C", [(8192, 4096), (8191, 4096), (9000, 4104), (70, 2048), (70, 2056), (70, 504)])
+def test_gather_scatter_row_copies(N, C):
+    # both sides of the 64 MB from which rows are streamed, and rows with and
+    # without a rest past the four loads in flight: bytes as torch moves them
+    say(f"[token_prune copies N={N} C={C}]")
+    g = torch.Generator(device="cuda").manual_seed(N + C)
+    x = torch.randn((1, N, C), generator=g, device="cuda", dtype=torch.float32).bfloat16()
+    idx = torch.sort(torch.randperm(N, generator=g, device="cuda")[: N // 2])[0]
+    pos = torch.full((1, N), -1, dtype=torch.int32, device="cuda")
+    pos[0, idx] = torch.arange(N // 2, dtype=torch.int32, device="cuda")
+    kept = sva.token_gather(x, idx.to(torch.int32)[None])
+    out = sva.token_scatter(-kept, pos, x)
+    want = x.clone()
+    want[0, idx] = -x[0, idx]
+    assert torch.equal(kept[0], x[0, idx]) and torch.equal(out, want)
 
 
 @pytest.mark.slow
