@@ -52,17 +52,22 @@ __device__ __forceinline__ uint32_t pack4_e4m3(float a, float b, float c, float 
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
-// The quantiser's tensors pass through once: their loads and the code stores are
-// non-temporal, so that they push no K or V that the statistics left in the
-// memory-side cache out of it (20 heads of 32,760 x 112: 181 us with plain loads
-// and stores, 164 us with non-temporal stores, 160 us with both).
-__device__ __forceinline__ uint4 load16_nt(const uint16_t* p) {
-  const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return make_uint4(v[0], v[1], v[2], v[3]);
+// Where the tensors exceed the caches (NT, see streams_past_caches) the
+// quantiser's loads and stores are non-temporal: they then push no K or V that
+// the statistics left in the memory-side cache out of it.
+template <bool NT>
+__device__ __forceinline__ uint4 load16(const uint16_t* p) {
+  if constexpr (NT) {
+    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+    return make_uint4(v[0], v[1], v[2], v[3]);
+  }
+  return *reinterpret_cast<const uint4*>(p);
 }
-__device__ __forceinline__ void store8_nt(uint8_t* p, uint2 o) {
+template <bool NT>
+__device__ __forceinline__ void store8(uint8_t* p, uint2 o) {
   const u32x2 v = {o.x, o.y};
-  __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(p));
+  if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(p));
+  else *reinterpret_cast<u32x2*>(p) = v;
 }
 
 // a float64 value rounded once to bf16 (nearest, ties to even), as bf16 bits
@@ -196,7 +201,7 @@ __global__ __launch_bounds__(kFinalThreads) void fp8_stats_final_kernel(Fp8Quant
 }
 
 // Q or smoothed K of one block
-template <int D, int S>
+template <int D, int S, bool NT>
 __device__ __forceinline__ void quant_qk_block(const Fp8QuantArgs& a, int row, bool is_k, float* red) {
   constexpr int DP = (D + 63) / 64 * 64;
   constexpr int TPR = DP / 8;
@@ -224,7 +229,7 @@ __device__ __forceinline__ void quant_qk_block(const Fp8QuantArgs& a, int row, b
   for (int p = 0; p < NP; ++p) {
     const int r = r0 + p * RPP;
     uint4 w = make_uint4(0, 0, 0, 0);
-    if (live && r < valid) w = load16_nt(src + (size_t)r * D + c * 8);
+    if (live && r < valid) w = load16<NT>(src + (size_t)r * D + c * 8);
     const float v[8] = {lo16(w.x), hi16(w.x), lo16(w.y), hi16(w.y), lo16(w.z), hi16(w.z), lo16(w.w), hi16(w.w)};
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -248,7 +253,7 @@ __device__ __forceinline__ void quant_qk_block(const Fp8QuantArgs& a, int row, b
     uint2 o;
     o.x = pack4_e4m3(ldexpf(x[p][0], -e), ldexpf(x[p][1], -e), ldexpf(x[p][2], -e), ldexpf(x[p][3], -e));
     o.y = pack4_e4m3(ldexpf(x[p][4], -e), ldexpf(x[p][5], -e), ldexpf(x[p][6], -e), ldexpf(x[p][7], -e));
-    store8_nt(dst + (size_t)r * DP + c * 8, o);             // rows past N, padding: zeros
+    store8<NT>(dst + (size_t)r * DP + c * 8, o);             // rows past N, padding: zeros
   }
 }
 
@@ -270,7 +275,7 @@ __device__ __forceinline__ void transpose4(const uint32_t (&x)[4], uint32_t (&y)
 // through 2-byte LDS reads, with stores 64 bytes apart, took 72 us for 20 heads
 // of 32,760 x 112 (3.2 TB/s), and Q and K in a kernel of their own 72 us more;
 // together they now take 100 us, 6.9 TB/s of reads and writes.
-template <int D, int S>
+template <int D, int S, bool NT>
 __device__ __forceinline__ void quant_v_block(const Fp8QuantArgs& a, int row, unsigned char* tile) {
   constexpr int DP = (D + 63) / 64 * 64;
   constexpr int TPR = DP / 8;
@@ -289,7 +294,7 @@ __device__ __forceinline__ void quant_v_block(const Fp8QuantArgs& a, int row, un
   for (int p = 0; p < NP; ++p) {
     const int r = r0 + p * RPP;
     w[p] = make_uint4(0, 0, 0, 0);
-    if (live && r < valid) w[p] = load16_nt(src + (size_t)r * D + c * 8);
+    if (live && r < valid) w[p] = load16<NT>(src + (size_t)r * D + c * 8);
   }
   int e[8];
 #pragma unroll
@@ -319,30 +324,37 @@ __device__ __forceinline__ void quant_v_block(const Fp8QuantArgs& a, int row, un
     transpose4(hi, y);
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-      store8_nt(dst + ((size_t)tt * DP + d + k) * 64 + t8 * 8, make_uint2(x[k], y[k]));
+      store8<NT>(dst + ((size_t)tt * DP + d + k) * 64 + t8 * 8, make_uint2(x[k], y[k]));
   }
 }
 
 // One workgroup per block of each tensor.  V and K blocks come first, in turns
 // and from the last head back, so that what the statistics read last is read
 // again while it is still in the 256 MB memory-side cache; then Q.
-template <int D, int S>
+template <int D, int S, bool NT>
 __global__ __launch_bounds__(kThreads) void fp8_quant_kernel(Fp8QuantArgs a) {
   constexpr int DP = (D + 63) / 64 * 64;
   __shared__ __attribute__((aligned(16))) unsigned char tile[S * (DP + 4)];
   __shared__ float red[kThreads / 64];
   const unsigned u = blockIdx.y * (unsigned)a.n_rows + blockIdx.x;
-  if (u >= 2u * a.n_rows) quant_qk_block<D, S>(a, u - 2u * a.n_rows, false, red);
-  else if (u & 1) quant_qk_block<D, S>(a, a.n_rows - 1 - (int)(u / 2), true, red);
-  else quant_v_block<D, S>(a, a.n_rows - 1 - (int)(u / 2), tile);
+  if (u >= 2u * a.n_rows) quant_qk_block<D, S, NT>(a, u - 2u * a.n_rows, false, red);
+  else if (u & 1) quant_qk_block<D, S, NT>(a, a.n_rows - 1 - (int)(u / 2), true, red);
+  else quant_v_block<D, S, NT>(a, a.n_rows - 1 - (int)(u / 2), tile);
 }
+
+// By the bytes of K and V (whole quantiser, us, plain / non-temporal): 32 MB 34.0 /
+// 35.4, 128 MB 81.2 / 73.3, 294 MB 181 / 160 (stores alone 164).
+bool streams_past_caches(const Fp8QuantArgs& a, int BH, int D) { return (int64_t)BH * a.N * D * 4 >= (64 << 20); }
 
 template <int D, int S>
 void launch_quant_ds(const Fp8QuantArgs& a, int BH, hipStream_t stream) {
   const int nseg = (a.N + kStatRows - 1) / kStatRows;
   hipLaunchKernelGGL((fp8_stats_partial_kernel<D>), dim3(nseg, BH), dim3(kThreads), 0, stream, a);
   hipLaunchKernelGGL((fp8_stats_final_kernel<D>), dim3(BH), dim3(kFinalThreads), 0, stream, a, nseg);
-  hipLaunchKernelGGL((fp8_quant_kernel<D, S>), dim3(a.n_rows, 3), dim3(kThreads), 0, stream, a);
+  if (streams_past_caches(a, BH, D))
+    hipLaunchKernelGGL((fp8_quant_kernel<D, S, true>), dim3(a.n_rows, 3), dim3(kThreads), 0, stream, a);
+  else
+    hipLaunchKernelGGL((fp8_quant_kernel<D, S, false>), dim3(a.n_rows, 3), dim3(kThreads), 0, stream, a);
 }
 
 }  // namespace
