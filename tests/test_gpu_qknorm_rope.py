@@ -102,6 +102,29 @@ def test_producer_in_place_equals_out_of_place():
     assert torch.equal(qo, q2) and torch.equal(ko, k2) and torch.equal(qp, qp2) and torch.equal(kp, kp2)
 
 
+@pytest.mark.parametrize("D,H,grid,S", [
+    (64, 15, (5, 70, 101), 64), (112, 9, (5, 70, 101), 64), (128, 8, (5, 70, 101), 64),
+    (128, 8, (11, 8, 400), 64),        # too wide for the table of a block: angles taken directly
+    (112, 9, (5, 70, 101), 128),
+])
+def test_producer_streamed_equals_one_head_at_a_time(D, H, grid, S):
+    # 64 MB and more stream past the caches, at S = 64 with Q and K in one
+    # workgroup; one head at a time takes the small form, which the oracle cases
+    # above pin: the same bits
+    n = grid[0] * grid[1] * grid[2]
+    assert H * n * D * 2 >= 64 << 20 > n * D * 2
+    say(f"[producer streamed D={D} S={S} {grid}]")
+    g = torch.Generator(device="cuda").manual_seed(D + S)
+    q, k = (torch.randn((1, H, n, D), generator=g, device="cuda").bfloat16() for _ in "qk")
+    gq, gk = (torch.rand(D, generator=g, device="cuda") + 0.5 for _ in "qk")
+    full = sva.qknorm_rope_pool(sva.problem(1, H, n, D, grid, S), q, k, gq, gk, EPS, BASE)
+    one = sva.problem(1, 1, n, D, grid, S)
+    for h in range(H):
+        part = sva.qknorm_rope_pool(one, q[:, h:h + 1].contiguous(), k[:, h:h + 1].contiguous(), gq, gk, EPS, BASE)
+        for x, y in zip(full, part):
+            assert torch.equal(x[:, h:h + 1], y), h
+
+
 @pytest.mark.slow
 def test_producer_full_size_sampled_heads():
     """The 64B-class shape: every head's summaries equal sva_pool_blocks of the
