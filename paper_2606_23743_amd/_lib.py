@@ -167,9 +167,19 @@ def max_keep(prob: Problem, sel: SelectParams) -> int:
 
 # ------------------------------------------------------------- device calls
 
+# A small call's time is this module's own: three launches of 3 to 9 us went out
+# every 41 us.  So torch is looked up once, a tensor that is as it should be
+# passes one test, tensors made here are not tested again, and the current stream
+# is asked for as a handle, without a stream object around it.
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t) -> Optional[int]:
@@ -177,8 +187,11 @@ def _ptr(t) -> Optional[int]:
 
 
 def _stream(stream) -> Optional[int]:
-    torch = _torch()
     if stream is None:
+        torch = _torch()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
@@ -202,6 +215,8 @@ def _record(stream, *tensors):
     memory of a tensor freed meanwhile (a workspace or output allocated here
     on the current stream, or an input the caller drops) from being handed to
     another allocation until the work enqueued on that stream has finished."""
+    if stream is None:
+        return
     s = _side_stream(stream)
     if s is None:
         return
@@ -214,6 +229,8 @@ def _record(stream, *tensors):
 
 def _need(t, dtype, shape, name):
     torch = _torch()
+    if isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.shape == shape and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if not t.is_cuda:
@@ -239,10 +256,12 @@ def pool_blocks(prob: Problem, q, k, q_pool=None, k_pool=None, stream=None) -> T
     pshape = (prob.batch, prob.heads, nb, prob.head_dim)
     if q_pool is None:
         q_pool = torch.empty(pshape, dtype=torch.float32, device=q.device)
+    else:
+        _need(q_pool, torch.float32, pshape, "q_pool")
     if k_pool is None:
         k_pool = torch.empty(pshape, dtype=torch.float32, device=q.device)
-    _need(q_pool, torch.float32, pshape, "q_pool")
-    _need(k_pool, torch.float32, pshape, "k_pool")
+    else:
+        _need(k_pool, torch.float32, pshape, "k_pool")
     _check(load().sva_pool_blocks(ctypes.byref(prob), _ptr(q), _ptr(k), _ptr(q_pool), _ptr(k_pool),
                                   _stream(stream)), "sva_pool_blocks")
     _record(stream, q, k, q_pool, k_pool)
@@ -263,17 +282,21 @@ def qknorm_rope_pool(prob: Problem, q_in, k_in, gamma_q, gamma_k, eps: float = 1
     _need(gamma_k, torch.float32, (prob.head_dim,), "gamma_k")
     if q_out is None:
         q_out = torch.empty_like(q_in)
+    else:
+        _need(q_out, torch.bfloat16, shp, "q_out")
     if k_out is None:
         k_out = torch.empty_like(k_in)
-    _need(q_out, torch.bfloat16, shp, "q_out")
-    _need(k_out, torch.bfloat16, shp, "k_out")
+    else:
+        _need(k_out, torch.bfloat16, shp, "k_out")
     pshape = (prob.batch, prob.heads, nb, prob.head_dim)
     if q_pool is None:
         q_pool = torch.empty(pshape, dtype=torch.float32, device=q_in.device)
+    else:
+        _need(q_pool, torch.float32, pshape, "q_pool")
     if k_pool is None:
         k_pool = torch.empty(pshape, dtype=torch.float32, device=q_in.device)
-    _need(q_pool, torch.float32, pshape, "q_pool")
-    _need(k_pool, torch.float32, pshape, "k_pool")
+    else:
+        _need(k_pool, torch.float32, pshape, "k_pool")
     rp = RopeParams(float(eps), float(rope_base))
     _check(load().sva_qknorm_rope_pool(ctypes.byref(prob), ctypes.byref(rp), _ptr(q_in), _ptr(k_in),
                                        _ptr(gamma_q), _ptr(gamma_k), _ptr(q_out), _ptr(k_out),
@@ -295,10 +318,12 @@ def select_blocks(prob: Problem, sel: SelectParams, q_pool, k_pool, kmax: Option
     dev = q_pool.device
     if kv_idx is None:
         kv_idx = torch.empty((prob.batch, prob.heads, nb, kmax), dtype=torch.int32, device=dev)
+    else:
+        _need(kv_idx, torch.int32, (prob.batch, prob.heads, nb, kmax), "kv_idx")
     if kv_count is None:
         kv_count = torch.empty((prob.batch, prob.heads, nb), dtype=torch.int32, device=dev)
-    _need(kv_idx, torch.int32, (prob.batch, prob.heads, nb, kmax), "kv_idx")
-    _need(kv_count, torch.int32, (prob.batch, prob.heads, nb), "kv_count")
+    else:
+        _need(kv_count, torch.int32, (prob.batch, prob.heads, nb), "kv_count")
     if want_mask and mask is None:
         mask = torch.empty((prob.batch, prob.heads, nb, nb), dtype=torch.uint8, device=dev)
     if mask is not None:
@@ -314,7 +339,7 @@ def _out_tensor(prob, like, out):
     torch = _torch()
     dt = torch.float32 if prob.out_dtype == SVA_F32 else torch.bfloat16
     if out is None:
-        out = torch.empty(_qkv_shape(prob), dtype=dt, device=like.device)
+        return torch.empty(_qkv_shape(prob), dtype=dt, device=like.device)
     _need(out, dt, _qkv_shape(prob), "out")
     return out
 
@@ -573,13 +598,16 @@ def token_select(x, keep_ratio: float, scores=None, kept_idx=None, kept_pos=None
     _need(x, torch.bfloat16, (B, N, C), "x")
     if scores is None:
         scores = torch.empty((B, N), dtype=torch.float64, device=x.device)
+    else:
+        _need(scores, torch.float64, (B, N), "scores")
     if kept_idx is None:
         kept_idx = torch.empty((B, k), dtype=torch.int32, device=x.device)
+    else:
+        _need(kept_idx, torch.int32, (B, k), "kept_idx")
     if kept_pos is None:
         kept_pos = torch.empty((B, N), dtype=torch.int32, device=x.device)
-    _need(scores, torch.float64, (B, N), "scores")
-    _need(kept_idx, torch.int32, (B, k), "kept_idx")
-    _need(kept_pos, torch.int32, (B, N), "kept_pos")
+    else:
+        _need(kept_pos, torch.int32, (B, N), "kept_pos")
     ws_bytes = token_select_workspace(t)
     if workspace is None:
         workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=x.device)
@@ -608,13 +636,16 @@ def token_select_noalloc(x, keep_ratio: float, scores=None, kept_idx=None, kept_
     _need(x, torch.bfloat16, (B, N, C), "x")
     if scores is None:
         scores = torch.empty((B, N), dtype=torch.float64, device=x.device)
+    else:
+        _need(scores, torch.float64, (B, N), "scores")
     if kept_idx is None:
         kept_idx = torch.empty((B, k), dtype=torch.int32, device=x.device)
+    else:
+        _need(kept_idx, torch.int32, (B, k), "kept_idx")
     if kept_pos is None:
         kept_pos = torch.empty((B, N), dtype=torch.int32, device=x.device)
-    _need(scores, torch.float64, (B, N), "scores")
-    _need(kept_idx, torch.int32, (B, k), "kept_idx")
-    _need(kept_pos, torch.int32, (B, N), "kept_pos")
+    else:
+        _need(kept_pos, torch.int32, (B, N), "kept_pos")
     _check(load().sva_token_select_noalloc(ctypes.byref(t), float(keep_ratio), _ptr(x), _ptr(scores),
                                            _ptr(kept_idx), _ptr(kept_pos), _stream(stream)),
            "sva_token_select_noalloc")
@@ -631,7 +662,8 @@ def token_gather(x, kept_idx, x_kept=None, stream=None):
     _need(kept_idx, torch.int32, (B, k), "kept_idx")
     if x_kept is None:
         x_kept = torch.empty((B, k, C), dtype=torch.bfloat16, device=x.device)
-    _need(x_kept, torch.bfloat16, (B, k, C), "x_kept")
+    else:
+        _need(x_kept, torch.bfloat16, (B, k, C), "x_kept")
     _check(load().sva_token_gather(ctypes.byref(tokens(B, N, C)), k, _ptr(x), _ptr(kept_idx),
                                    _ptr(x_kept), _stream(stream)), "sva_token_gather")
     _record(stream, x, kept_idx, x_kept)
@@ -649,7 +681,8 @@ def token_scatter(y_kept, kept_pos, base, out=None, stream=None):
     _need(base, torch.bfloat16, (B, N, C), "base")
     if out is None:
         out = torch.empty_like(base)
-    _need(out, torch.bfloat16, (B, N, C), "out")
+    else:
+        _need(out, torch.bfloat16, (B, N, C), "out")
     _check(load().sva_token_scatter(ctypes.byref(tokens(B, N, C)), k, _ptr(y_kept), _ptr(kept_pos),
                                     _ptr(base), _ptr(out), _stream(stream)), "sva_token_scatter")
     _record(stream, y_kept, kept_pos, base, out)
