@@ -79,12 +79,13 @@ __device__ __forceinline__ float row_sum(float x) {
 }
 
 // ss / D: a product where D is a power of two, else with the quotient's residual
+// (a sum that overflowed has none and stays infinite: its row becomes zero)
 template <int D>
 __device__ __forceinline__ float mean_of(float ss) {
   constexpr float r = 1.0f / (float)D;
   const float q = ss * r;
   if constexpr ((D & (D - 1)) == 0) return q;
-  return fmaf(fmaf(-(float)D, q, ss), r, q);
+  return q < INFINITY ? fmaf(fmaf(-(float)D, q, ss), r, q) : q;
 }
 
 // 1 / sqrt(a), the hardware's (1 ulp); it may not take subnormal a

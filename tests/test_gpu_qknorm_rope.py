@@ -125,6 +125,24 @@ def test_producer_streamed_equals_one_head_at_a_time(D, H, grid, S):
             assert torch.equal(x[:, h:h + 1], y), h
 
 
+@pytest.mark.parametrize("D", [64, 112, 128])
+def test_producer_row_whose_sum_of_squares_overflows_is_zero(D):
+    # 1e25 squared is past float32's range: the mean is infinite, its reciprocal
+    # root zero, so the row's outputs are zero and the other rows keep theirs
+    n, row = 96, 37
+    prob = sva.problem(1, 1, n, D, (2, 6, 8), 64)
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k = (torch.randn((1, 1, n, D), generator=g, device="cuda").bfloat16() for _ in "qk")
+    gamma = torch.ones(D, device="cuda")
+    want = [x.clone() for x in sva.qknorm_rope_pool(prob, q, k, gamma, gamma, EPS, BASE)[:2]]
+    for x, y in zip((q, k), want):
+        x[0, 0, row] = 1e25
+        y[0, 0, row] = 0
+    got = sva.qknorm_rope_pool(prob, q, k, gamma, gamma, EPS, BASE)
+    for x, y in zip(got, want):
+        assert torch.equal(x, y)
+
+
 @pytest.mark.slow
 def test_producer_full_size_sampled_heads():
     """The 64B-class shape: every head's summaries equal sva_pool_blocks of the
