@@ -221,7 +221,7 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
         }
       }
       const int nvalid = __builtin_amdgcn_readfirstlane(N - nkey0);
-      if (nvalid < CK && active(un)) {
+      if (__builtin_expect(nvalid < CK && active(un), 0)) {
         asm volatile("");
         mask_tail16(snext, nvalid, lane);
       }

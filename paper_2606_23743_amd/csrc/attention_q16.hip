@@ -201,7 +201,7 @@ void attn_q16_kernel(AttnArgs a) {
         pv(pop, &Vs[c][0]);
         __builtin_amdgcn_s_setprio(0);
         const int nvalid = __builtin_amdgcn_readfirstlane(N - nkey0);
-        if (nvalid < CK) {
+        if (__builtin_expect(nvalid < CK, 0)) {
           asm volatile("");        // keep this a real (rarely taken) branch, not select code
           mask_tail16(snext, nvalid, lane);
         }
@@ -237,7 +237,7 @@ void attn_q16_kernel(AttnArgs a) {
         softmax(sacc, pop);
         pv(pop, &Vs[c][0]);
         const int nvalid = __builtin_amdgcn_readfirstlane(N - nkey0);
-        if (nvalid < CK) {
+        if (__builtin_expect(nvalid < CK, 0)) {
           asm volatile("");        // keep this a real (rarely taken) branch, not select code
           mask_tail16(snext, nvalid, lane);
         }

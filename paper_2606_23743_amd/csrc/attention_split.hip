@@ -112,9 +112,9 @@ void attn_split_kernel(AttnArgs a, int tiles_per_head, int n_tiles) {
   // keys of the current chunk and of the two after it
   int kc = key_of(block_of(c0), c0), kn = key_of(block_of(c0 + 1), c0 + 1), kn2 = key_of(block_of(c0 + 2), c0 + 2);
   if (steps > 0) {
-    load_tile<true>(ld, 0, kc);
-    load_tile<false>(ld, 0, kc);
-    load_tile<true>(ld, 1, kn);
+    load_tile<true, false>(ld, 0, kc);
+    load_tile<false, false>(ld, 0, kc);
+    load_tile<true, false>(ld, 1, kn);
     wait_vmcnt<0>();
     wg_barrier();
     qk16<D>(sacc, ks, koff, qop);
@@ -132,8 +132,8 @@ void attn_split_kernel(AttnArgs a, int tiles_per_head, int n_tiles) {
       const int c = c0 + s0 + p;
       wait_vmcnt_lds_idle<0>();
       wg_barrier();
-      load_tile<true>(ld, p, kn2);
-      load_tile<false>(ld, 1 - p, kn);
+      load_tile<true, false>(ld, p, kn2);
+      load_tile<false, false>(ld, 1 - p, kn);
       const int block3 = block_of(c + 3);    // an LDS read: used at the end of the step
       f32x4 snext[2][2];
       qk16<D>(snext, ks + (1 - p) * CT, koff, qop);
