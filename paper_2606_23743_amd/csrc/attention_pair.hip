@@ -247,7 +247,7 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
     for (int s = 0; s < (has_b ? 2 : 1); ++s) {
       const int row = row0 + s;
       const int32_t* idx = a.kv_idx + (size_t)row * a.kmax;
-      general_walk16<D, S, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase,
+      general_walk16<D, S, 2, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase,
                                     min(max(a.kv_count[row], 0), a.kmax),
                                     [&](int t) {
                                       const int b = __builtin_amdgcn_readfirstlane(idx[t]);

@@ -1,11 +1,19 @@
-// Block-sparse (and dense) flash attention on mfma_f32_16x16x32_bf16, 32
-// queries per wave, two waves per SIMD (Section 4.2.2: kept blocks computed
-// exactly; Appendix A.2.2: dense FlashAttention fallback).
+// Block-sparse (and dense) flash attention on mfma_f32_16x16x32_bf16 (Section
+// 4.2.2: kept blocks computed exactly; Appendix A.2.2: dense FlashAttention
+// fallback).
 //
-// A workgroup is one query block of S tokens with S/32 waves of 32 queries.
-// Each wave's state (O^T 4*D/16*2 registers, Q^T, S^T and P of a key chunk)
-// fits in 256 registers, so two workgroups share a CU with two waves on every
-// SIMD.
+// A workgroup is one query block of S tokens with S/32 waves of 32 queries
+// (QT = 2 tiles of 16).  Each wave's state (O^T 4*D/16*2 registers, Q^T, S^T and
+// P of a key chunk) fits in 256 registers, so two workgroups share a CU with two
+// waves on every SIMD.
+//
+// Calls with few query blocks (few_query_tiles, attention.hip) leave wave slots
+// empty, and what bounds them is one wave's chain of 32-key steps (S products,
+// softmax, PV products and the waits between them).  There a workgroup is 64
+// queries with four waves of 16 (QT = 1): twice the waves, each step with half
+// the products and half the softmax.  A query's arithmetic and its order are
+// those of the other form, so its bits do not depend on which one ran.  20 heads
+// of 1560 dense tokens x 112: 44.9 us with 32 queries per wave, 35.3 with 16.
 //
 // Keys are processed in 32-key chunks staged in LDS, chunk c of a kept block
 // in stage c (S/32 stages), filled by buffer_load ... lds straight from global
@@ -41,12 +49,13 @@ namespace {
 
 using namespace attn;
 
-template <int D, int S, bool SPARSE, bool OUT_F32>
-__global__ __launch_bounds__(2 * S) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, int S, int QT, bool SPARSE, bool OUT_F32>
+__global__ __launch_bounds__(QT == 2 ? 2 * S : 256) __attribute__((amdgpu_waves_per_eu(2, QT == 2 ? 2 : 4)))
 void attn_q16_kernel(AttnArgs a) {
   using G = Geo<D>;
   using G16 = Geo16<D>;
-  constexpr int NW = S / 32;                 // waves per workgroup
+  constexpr int TQ = QT == 2 ? S : 64;       // queries per workgroup
+  constexpr int NW = TQ / (16 * QT);         // waves per workgroup
   constexpr int CK = 32;                     // keys per staged chunk
   constexpr int NCK = S / CK;                // chunks per block
   constexpr int NST = NCK;                   // LDS stages: chunk c of a block in stage c
@@ -65,20 +74,21 @@ void attn_q16_kernel(AttnArgs a) {
   const int N = a.N, nB = a.nB;
   const float sl2 = a.scale_log2;
 
-  constexpr bool kSegments = SPARSE && S == 128;
-  const int wg = kSegments ? xcd_remap_segments(blockIdx.x, a.n_rows, 128) : xcd_remap(blockIdx.x, a.n_rows);
-  const int rowl = __builtin_amdgcn_readfirstlane(wg);   // (b*H + h)*nB + logical block
-  const int bh = rowl / nB;
-  const int i = SPARSE ? frame_tile_order(rowl - bh * nB, nB, a.frame_blocks, 8, 4) : rowl - bh * nB;
-  const int row = bh * nB + i;
+  constexpr bool kSegments = SPARSE && QT == 2 && S == 128;
+  const int wg = kSegments ? xcd_remap_segments(blockIdx.x, gridDim.x, 128) : xcd_remap(blockIdx.x, gridDim.x);
+  const int tl = __builtin_amdgcn_readfirstlane(wg);     // (b*H + h)*tiles + logical tile
+  const int tiles = QT == 2 ? nB : (N + TQ - 1) / TQ;    // query tiles per head
+  const int bh = tl / tiles;
+  const int tile = SPARSE && QT == 2 ? frame_tile_order(tl - bh * tiles, nB, a.frame_blocks, 8, 4) : tl - bh * tiles;
+  const int row = bh * nB + tile * TQ / S;               // its query block's list
   const size_t head = (size_t)bh * N * D;
   const uint16_t* Qh = a.q + head;
   const uint16_t* Kh = a.k + head;
   const uint16_t* Vh = a.v + head;
 
-  // ---- Q^T operands: queries i*S + w*32 + 0..31 ----
-  const int qbase = i * S + w * 32;
-  bf16x8 qop[2][G16::KS];
+  // ---- Q^T operands: queries qbase + 0 .. 16*QT - 1 ----
+  const int qbase = tile * TQ + w * 16 * QT;
+  bf16x8 qop[QT][G16::KS];
   load_q16<D>(qop, Qh, qbase, N, lane);
 
   // ---- the kept-block list ----
@@ -111,21 +121,18 @@ void attn_q16_kernel(AttnArgs a) {
   int koff[G16::KS], voff[G16::DT];
   operand_offsets16<D>(lane, koff, voff);
 
-  float m_ref[2] = {0.0f, 0.0f};     // reference max (log2 units) per query tile
-  float l_part[2] = {0.0f, 0.0f};    // this lane's quarter of each row sum
-  f32x4 oacc[G16::DT][2];
-#pragma unroll
-  for (int dt = 0; dt < G16::DT; ++dt) oacc[dt][0] = oacc[dt][1] = f32x4{};
+  float m_ref[QT] = {};              // reference max (log2 units) per query tile
+  float l_part[QT] = {};             // this lane's quarter of each row sum
+  f32x4 oacc[G16::DT][QT] = {};
 
-  auto qk = [&](f32x4 (&s)[2][2], const unsigned char* kt) { qk16<D>(s, kt, koff, qop); };
-  auto softmax = [&](const f32x4 (&s)[2][2], bf16x8 (&pop)[2]) { softmax16(s, pop, l_part, m_ref, sl2); };
-  auto pv = [&](const bf16x8 (&pop)[2], const unsigned char* vt) { pv16<D>(pop, vt, voff, oacc); };
-  auto take = [](f32x4 (&dst)[2][2], const f32x4 (&src)[2][2]) {
+  auto qk = [&](f32x4 (&s)[2][QT], const unsigned char* kt) { qk16<D>(s, kt, koff, qop); };
+  auto softmax = [&](const f32x4 (&s)[2][QT], bf16x8 (&pop)[QT]) { softmax16(s, pop, l_part, m_ref, sl2); };
+  auto pv = [&](const bf16x8 (&pop)[QT], const unsigned char* vt) { pv16<D>(pop, vt, voff, oacc); };
+  auto take = [](f32x4 (&dst)[2][QT], const f32x4 (&src)[2][QT]) {
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      dst[x][0] = src[x][0];
-      dst[x][1] = src[x][1];
-    }
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) dst[x][qt] = src[x][qt];
   };
 
   // ---- pipeline over (kept block, chunk) ----
@@ -159,9 +166,7 @@ void attn_q16_kernel(AttnArgs a) {
       jn = itn < count ? raw_at(itn) : -1;
     }
   };
-  f32x4 sacc[2][2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x) sacc[x][0] = sacc[x][1] = f32x4{};
+  f32x4 sacc[2][QT] = {};
   if (it < count) {
     if constexpr (PIPE) wait_vmcnt<2 * NUW * (PD - 1)>();
     else wait_vmcnt<0>();
@@ -190,8 +195,8 @@ void attn_q16_kernel(AttnArgs a) {
         else fetch((c + PD) % NST, jn >= 0 ? jn * S + (c + PD - NCK) * CK : 0);
         if (c == 0) jnn = itnn < count ? raw_at(itnn) : -1;
         const int nkey0 = c + 1 < NCK ? j * S + (c + 1) * CK : (jn >= 0 ? jn * S : 0);
-        f32x4 snext[2][2];
-        bf16x8 pop[2];
+        f32x4 snext[2][QT];
+        bf16x8 pop[QT];
         qk(snext, &Ks[(c + 1) % NST][0]);
         softmax(sacc, pop);
         // The PV products issue at raised wave priority, ahead of the other
@@ -231,8 +236,8 @@ void attn_q16_kernel(AttnArgs a) {
         else fetch_v(0, jn >= 0 ? jn * S : 0);
         if (c == 0) jnn = itnn < count ? raw_at(itnn) : -1;
         const int nkey0 = c + 1 < NCK ? j * S + (c + 1) * CK : (jn >= 0 ? jn * S : 0);
-        f32x4 snext[2][2];
-        bf16x8 pop[2];
+        f32x4 snext[2][QT];
+        bf16x8 pop[QT];
         qk(snext, &Ks[(c + 1) % NST][0]);
         softmax(sacc, pop);
         pv(pop, &Vs[c][0]);
@@ -251,45 +256,52 @@ void attn_q16_kernel(AttnArgs a) {
 
   // ---- epilogue: overflow check, then O = O^T / l and LSE ----
   if (threadIdx.x == 0) wg_bad = 0;
-  float l_tot[2];
-  l_tot[0] = quad_sum(l_part[0]);
-  l_tot[1] = quad_sum(l_part[1]);
+  float l_tot[QT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) l_tot[qt] = quad_sum(l_part[qt]);
   const bool bad = overflowed16<D>(l_tot, oacc);
   __syncthreads();
   if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&wg_bad, 1);
   __syncthreads();
   if (wg_bad) {
-    general_walk16<D, S, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase, count,
+    general_walk16<D, S, QT, OUT_F32>(a, ld, &Ks[0][0], &Vs[0][0], koff, voff, bh, qbase, count,
                                   [&](int t) { const int b = raw_at(t); return in_range(b) ? b : -1; }, true);
     return;
   }
-  const bool has[2] = {count > 0 && l_tot[0] > 0.0f, count > 0 && l_tot[1] > 0.0f};
+  bool has[QT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) has[qt] = count > 0 && l_tot[qt] > 0.0f;
   store_query16<D, OUT_F32>(a.out, a.lse, head, (size_t)bh * N, qbase, N, oacc, l_tot, m_ref, has, lane);
 }
 
-template <int D, int S>
+template <int D, int S, int QT>
 hipError_t launch_q16(const Dims& d, bool sparse, const AttnArgs& a, hipStream_t stream) {
-  dim3 grid(a.n_rows), block(2 * S);
+  dim3 grid(QT == 2 ? a.n_rows : d.B * d.H * ((d.N + 63) / 64)), block(QT == 2 ? 2 * S : 256);
   if (sparse) {
-    if (d.out_f32) hipLaunchKernelGGL((attn_q16_kernel<D, S, true, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((attn_q16_kernel<D, S, true, false>), grid, block, 0, stream, a);
+    if (d.out_f32) hipLaunchKernelGGL((attn_q16_kernel<D, S, QT, true, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((attn_q16_kernel<D, S, QT, true, false>), grid, block, 0, stream, a);
   } else {
-    if (d.out_f32) hipLaunchKernelGGL((attn_q16_kernel<D, S, false, true>), grid, block, 0, stream, a);
-    else hipLaunchKernelGGL((attn_q16_kernel<D, S, false, false>), grid, block, 0, stream, a);
+    if (d.out_f32) hipLaunchKernelGGL((attn_q16_kernel<D, S, QT, false, true>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((attn_q16_kernel<D, S, QT, false, false>), grid, block, 0, stream, a);
   }
   return hipGetLastError();
 }
 
+template <int D, int S>
+hipError_t launch_ds(const Dims& d, bool sparse, bool narrow, const AttnArgs& a, hipStream_t stream) {
+  return narrow ? launch_q16<D, S, 1>(d, sparse, a, stream) : launch_q16<D, S, 2>(d, sparse, a, stream);
+}
+
 }  // namespace
 
-hipError_t launch_attention_q16(const Dims& d, bool sparse, const AttnArgs& a, hipStream_t stream) {
+hipError_t launch_attention_q16(const Dims& d, bool sparse, bool narrow, const AttnArgs& a, hipStream_t stream) {
   switch (d.D * 1000 + d.S) {
-    case 64128: return launch_q16<64, 128>(d, sparse, a, stream);
-    case 112128: return launch_q16<112, 128>(d, sparse, a, stream);
-    case 128128: return launch_q16<128, 128>(d, sparse, a, stream);
-    case 64064: return launch_q16<64, 64>(d, sparse, a, stream);
-    case 112064: return launch_q16<112, 64>(d, sparse, a, stream);
-    case 128064: return launch_q16<128, 64>(d, sparse, a, stream);
+    case 64128: return launch_ds<64, 128>(d, sparse, narrow, a, stream);
+    case 112128: return launch_ds<112, 128>(d, sparse, narrow, a, stream);
+    case 128128: return launch_ds<128, 128>(d, sparse, narrow, a, stream);
+    case 64064: return launch_ds<64, 64>(d, sparse, narrow, a, stream);
+    case 112064: return launch_ds<112, 64>(d, sparse, narrow, a, stream);
+    case 128064: return launch_ds<128, 64>(d, sparse, narrow, a, stream);
     default: return hipErrorInvalidValue;
   }
 }

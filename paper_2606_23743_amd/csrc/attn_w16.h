@@ -1,6 +1,6 @@
 // Per-chunk arithmetic of the bf16 attention kernels on mfma_f32_16x16x32_bf16
 // (attention_q16.hip, attention_pair.hip): QT tiles of 16 queries per wave
-// (two: 32 queries), one staged 32-key chunk at a time.
+// (two; one in calls with few query blocks), one staged 32-key chunk at a time.
 //
 // Lane l = 16g + i (group g = 0..3, column i = 0..15).  For query tile qt the
 // lane holds query qt*16 + i:
@@ -261,7 +261,7 @@ __device__ __forceinline__ void store_query16(void* out, float* lse, size_t head
 // around it; one chunk at a time through stage 0, K twice (the block's maximum,
 // then its probabilities).  Several times slower than the fast loop, on rows
 // that real inputs do not have.
-template <int D, int S, bool OUT_F32, class Loader, class BlockAt>
+template <int D, int S, int QT, bool OUT_F32, class Loader, class BlockAt>
 __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& ld, const unsigned char* ks,
                                                const unsigned char* vs, const int (&koff)[Geo16<D>::KS],
                                                const int (&voff)[Geo16<D>::DT], int bh, int qbase, int count,
@@ -269,7 +269,7 @@ __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& 
   const int N = a.N, lane = ld.lane;
   const size_t head = (size_t)bh * N * D;
 #pragma unroll 1
-  for (int half = 0; half < 2; ++half) {
+  for (int half = 0; half < QT; ++half) {
     bf16x8 qop[1][Geo16<D>::KS];
     load_q16<D>(qop, a.q + head, qbase + half * 16, mine ? N : 0, lane);
     float m_run[1] = {-INFINITY}, l_part[1] = {0.0f};

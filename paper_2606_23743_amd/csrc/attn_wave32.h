@@ -59,7 +59,7 @@ __device__ __forceinline__ void buffer_to_lds(const __amdgpu_buffer_rsrc_t& rs, 
 }
 
 // one tensor's pieces (TK: K, else V) of the chunk starting at key0 into stage st
-template <bool TK, bool HINT = true, int D, int NUW, int CT, bool V16>
+template <bool TK, int D, int NUW, int CT, bool V16>
 __device__ __forceinline__ void load_tile(const ChunkLoader<D, NUW, CT, V16>& f, int st, int key0) {
   using G = Geo<D>;
   const __amdgpu_buffer_rsrc_t& rs = TK ? f.krs : f.vrs;
@@ -67,10 +67,8 @@ __device__ __forceinline__ void load_tile(const ChunkLoader<D, NUW, CT, V16>& f,
   key0 = __builtin_amdgcn_readfirstlane(key0);
   // Only the sequence's last chunk takes the other side.  Told so, the compiler lays
   // it out of the loop: 48 heads of 111,600 x 128 at 15% 0.7% above the kernel without
-  // the general walk, now 0.2% (level); other sparse layers 0.2-1.2% less.  Short walks are
-  // better without (HINT false): 1560 dense tokens x 20 heads 30.8 us, hinted 31.8.
-  const bool whole = key0 + 32 <= f.N;
-  if (HINT ? __builtin_expect(whole, 1) : whole) {
+  // the general walk, now 0.2% (level); other sparse layers 0.2-1.2% less.
+  if (__builtin_expect(key0 + 32 <= f.N, 1)) {
 #pragma unroll
     for (int v = 0; v < NUW; ++v) buffer_to_lds(rs, base + (f.w * NUW + v) * 1024, TK ? f.kgv[v] : f.vgv[v], key0 * D * 2);
   } else {

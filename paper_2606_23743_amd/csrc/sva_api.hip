@@ -46,7 +46,6 @@ int check_problem(const sva_problem* p, Dims* d) {
     d->nB = (int)nB;
     d->frame_tokens = (int)((int64_t)p->grid_h * p->grid_w > INT32_MAX ? INT32_MAX
                                                                         : (int64_t)p->grid_h * p->grid_w);
-    d->call_pairs = p->batch * p->heads;
     d->scale = p->softmax_scale > 0.0 ? p->softmax_scale : 1.0 / sqrt((double)p->head_dim);
     d->out_f32 = p->out_dtype == SVA_F32;
   }

@@ -13,7 +13,6 @@ namespace sva {
 struct Dims {
   int B, H, N, D, S, nB;
   int frame_tokens;   // grid_h * grid_w
-  int call_pairs;     // B * H of the whole call, which a pass over some of its (b, h) pairs keeps
   double scale;       // softmax scale c (resolved, > 0)
   bool out_f32;
 };
@@ -27,9 +26,9 @@ struct SelectRule {
   int n_forced; // mass: forced first-frame blocks 0 .. n_forced-1
 };
 
-// 32-queries-per-wave, two-waves-per-SIMD attention with a fixed reference max
-// on 16x16x32 products; attention_q16.hip.
-hipError_t launch_attention_q16(const Dims& d, bool sparse, const AttnArgs& a, hipStream_t stream);
+// Attention with a fixed reference max on 16x16x32 products, 32 queries per wave
+// (narrow: 16, for calls with few query blocks); attention_q16.hip.
+hipError_t launch_attention_q16(const Dims& d, bool sparse, bool narrow, const AttnArgs& a, hipStream_t stream);
 
 // Sparse attention for 64-token blocks, two neighbouring query blocks per
 // workgroup walking the union of their lists; attention_pair.hip.  Used when
@@ -37,12 +36,6 @@ hipError_t launch_attention_q16(const Dims& d, bool sparse, const AttnArgs& a, h
 // long sequences).
 bool pair_attention_fits(const Dims& d, int kmax);
 hipError_t launch_attention_pair(const Dims& d, const AttnArgs& a, hipStream_t stream);
-
-// Attention for calls with few query blocks: 64-query tiles whose keys are
-// divided among `groups` (2 or 4) groups of waves of a workgroup;
-// attention_split.hip.  Sparse rows of at most kSplitMaxList entries.
-constexpr int kSplitMaxList = 2048;
-hipError_t launch_attention_split(const Dims& d, int groups, bool sparse, const AttnArgs& a, hipStream_t stream);
 
 // fp8 (e4m3) quantisation and attention; fp8_quant.hip, attention_fp8.hip.
 // Codes: q8, k8 [B, H, Np, D]; v8 [B, H, Np/64, D, 64] (Np = nB * S, padding

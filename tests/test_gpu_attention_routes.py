@@ -1,7 +1,6 @@
 """bf16 attention along each of its kernels at the sizes where they hand over to
-one another: the key-split kernel (few query tiles, two and four groups), the
-single-block kernels above it, and the block-pair kernel (long rows of long
-sequences).  Every case against the oracle, with the general list forms (empty,
+one another: 16 queries per wave (few query tiles), the single-block kernels
+above it, and the block-pair kernel (long rows of long sequences).  Every case against the oracle, with the general list forms (empty,
 unsorted, out of range, repeated, the partial last block) and with a block whose
 logits overflow the fixed reference.
 """
@@ -59,14 +58,14 @@ def _arrays(rows, H, nb, kmax):
     return torch.from_numpy(idx).cuda(), torch.from_numpy(cnt).cuda()
 
 
-# (D, S, heads, grid, kmax): two groups from 16 chunks, four from 24, none past
-# 512 tiles; the last block holds 5 tokens or the sequence is under one block
+# (D, S, heads, grid, kmax): both sides of 512 tiles; the last block holds 5
+# tokens or the sequence is under one block
 @pytest.mark.parametrize("D,S,H,grid,kmax", [
     (64, 64, 2, (3, 43, 5), 8), (112, 64, 2, (3, 43, 5), 7), (112, 64, 2, (3, 43, 5), 11), (128, 64, 2, (1, 1, 901), 12),
     (128, 64, 2, (1, 1, 901), 15), (112, 128, 2, (1, 1, 901), 4), (128, 128, 2, (1, 1, 901), 8), (128, 128, 2, (1, 1, 901), 3),
     (64, 128, 1, (1, 1, 901), 7), (128, 128, 1, (1, 3, 1), 1), (128, 64, 18, (1, 1, 901), 8),
     (64, 128, 34, (1, 1, 901), 4), (112, 64, 35, (1, 1, 901), 8), (128, 128, 35, (1, 1, 901), 6)])
-def test_split_and_single_general_lists(D, S, H, grid, kmax):
+def test_narrow_and_wide_general_lists(D, S, H, grid, kmax):
     wl = SC(f"routes_{D}_{S}_{H}_{kmax}", 1, H, D, grid, S, "topk", topk=1, seed=500 + kmax)
     bits = inputs.generate(wl)
     dev = device_inputs(bits)
@@ -85,12 +84,41 @@ def test_split_and_single_general_lists(D, S, H, grid, kmax):
     _check(out, lse, f64, lambda h, i: range(nb), S, scale_of(wl), [(h, i) for h in {0, H - 1} for i in range(nb)])
 
 
+@pytest.mark.parametrize("D,S", [(64, 64), (112, 64), (128, 64), (64, 128), (112, 128), (128, 128)])
+@pytest.mark.parametrize("f32", [False, True])
+def test_a_head_does_not_depend_on_its_call(D, S, f32):
+    """One head alone (25 query tiles), in a call of 22 heads (550 tiles, past the
+    512 from which 32 queries share a wave) and, sparse, with its lists in
+    longer rows: the same bits, dense and sparse."""
+    H, N = 22, 1560
+    say(f"[routes one head D={D} S={S} f32={f32}]")
+    g = torch.Generator(device="cuda").manual_seed(D + S)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in "qkv")
+    nb = -(-N // S)
+    kept = 5
+    idx = torch.rand((1, H, nb, nb), generator=g, device="cuda").argsort(-1)[..., :kept].sort(-1)[0].int().contiguous()
+    cnt = torch.full((1, H, nb), kept, dtype=torch.int32, device="cuda")
+    dt = "f32" if f32 else "bf16"
+    every, one = (sva.problem(1, h, N, D, (1, 1, N), S, out_dtype=dt) for h in (H, 1))
+    dense = sva.dense_attention(every, q, k, v, want_lse=True)
+    sparse = sva.sparse_attention(every, q, k, v, idx, cnt, want_lse=True)
+    for h in (0, H - 1):
+        qh, kh, vh = (x[:, h:h + 1].contiguous() for x in (q, k, v))
+        for x, y in zip(dense, sva.dense_attention(one, qh, kh, vh, want_lse=True)):
+            assert torch.equal(x[:, h:h + 1], y), h
+        for kmax in (kept, nb, 4 * nb):
+            rows = torch.full((1, 1, nb, kmax), -1, dtype=torch.int32, device="cuda")
+            rows[..., :kept] = idx[:, h:h + 1]
+            got = sva.sparse_attention(one, qh, kh, vh, rows, cnt[:, h:h + 1].contiguous(), want_lse=True)
+            for x, y in zip(sparse, got):
+                assert torch.equal(x[:, h:h + 1], y), (h, kmax)
+
+
 @pytest.mark.parametrize("D,S,H", [(128, 64, 65), (64, 128, 65), (112, 64, 65), (128, 128, 65), (128, 64, 2),
                                    (64, 64, 1), (112, 128, 1)])
 def test_overflow_is_walked_again(D, S, H):
     """A later kept block whose logits exceed the first chunk's reference by
-    about 1000 (log2 units), with more tiles than the split kernel takes (65
-    heads) and within it."""
+    about 1000 (log2 units), with more than 512 query tiles (65 heads) and fewer."""
     wl = SC(f"routes_over_{D}_{S}_{H}", 1, H, D, (4, 8, 16), S, "topk", topk=2, seed=520)
     bits = inputs.generate(wl)
     f = {n: inputs.bf16_bits_to_f32(bits[n]).copy() for n in ("q", "k", "v")}
@@ -102,7 +130,7 @@ def test_overflow_is_walked_again(D, S, H):
     nb = 512 // S
     hot = list(range(384 // S, nb))
     rows = lambda i: [0] + hot + [1] if i * S >= 128 else [0, 1]   # noqa: E731
-    idx, cnt = _arrays(rows, H, nb, 1024 // S)       # rows of 32 chunks: split where the tiles are few
+    idx, cnt = _arrays(rows, H, nb, 1024 // S)
     out, lse = sva.sparse_attention(sva.problem_for(wl), dev["q"], dev["k"], dev["v"], idx, cnt, want_lse=True)
     torch.cuda.synchronize()
     assert lse.max().item() > 400.0                  # the regime this test is about
@@ -128,7 +156,7 @@ def test_pairs_of_long_sequences():
     o1, l1 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide, cnt, want_lse=True)
     o2, l2 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide[..., :12].contiguous(), cnt, want_lse=True)
     torch.cuda.synchronize()
-    assert H * nb > 512                              # the short rows run unsplit
+    assert H * nb > 512                              # 32 queries per wave
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
     _check(o1, l1, f64, lambda h, i: asc[i], S, scale_of(wl), [(0, i) for i in (0, 1, 3, 256, nb - 2, nb - 1)])
 

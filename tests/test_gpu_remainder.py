@@ -191,12 +191,15 @@ def test_workspace_is_reusable_and_sized_by_the_call():
 
 
 @pytest.mark.parametrize("out_dtype", ["bf16", "f32"])
-def test_smaller_workspace_runs_head_groups(out_dtype):
+@pytest.mark.parametrize("grid", [(2, 6, 11), (4, 40, 40)])
+def test_smaller_workspace_runs_head_groups(grid, out_dtype):
     """A workspace for fewer (batch, head) pairs than the problem has: the call
     does the pairs in groups of as many as fit (here 2, 2, 2; 4, 2; 1 x 6) and
     must give exactly the one-pass result, output and LSE, whichever output
-    type; below one pair's size the binding refuses."""
-    wl = SC("rem_groups", 2, 3, 128, (2, 6, 11), 64, "topk", keep_ratio=0.3, seed=311)
+    type; below one pair's size the binding refuses.  At 6400 tokens the one pass
+    has 600 query tiles, past the 512 up to which the kept part takes 16 queries
+    per wave, and every group fewer."""
+    wl = SC("rem_groups", 2, 3, 128, grid, 64, "topk", keep_ratio=0.3, seed=311)
     prob = sva.problem_for(wl)
     if out_dtype == "f32":
         prob.out_dtype = 1
