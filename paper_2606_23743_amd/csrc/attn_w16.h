@@ -259,8 +259,9 @@ __device__ __forceinline__ void store_query16(void* out, float* lse, size_t head
 // first query; block_at(t): the t-th list entry, negative where it is skipped.
 // 16 queries at a time, so that it needs fewer registers than the fast loop
 // around it; one chunk at a time through stage 0, K twice (the block's maximum,
-// then its probabilities).  Several times slower than the fast loop, on rows
-// that real inputs do not have.
+// then its probabilities).  Padding is zeros here, not the copies that the fast
+// loop multiplies by zeros: a block with Inf in K or V comes here because of them.
+// Several times slower than the fast loop, on rows that real inputs do not have.
 template <int D, int S, int QT, bool OUT_F32, class Loader, class BlockAt>
 __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& ld, const unsigned char* ks,
                                                const unsigned char* vs, const int (&koff)[Geo16<D>::KS],
@@ -291,6 +292,8 @@ __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& 
           load_tile<true>(ld, 0, key0);
           load_tile<false>(ld, 0, key0);
           wait_vmcnt<0>();
+          clear_absent(ld, 0, N - key0);
+          wait_vmcnt_lds_idle<0>();
           wg_barrier();
           f32x4 s[2][1];
           qk16<D>(s, ks, koff, qop);

@@ -97,6 +97,26 @@ __device__ __forceinline__ void load_chunk(const ChunkLoader<D, NUW, CT, V16>& f
   load_tile<false>(f, st, key0);
 }
 
+// Zeros over what load_chunk put into stage st for channels past D and for rows
+// past the sequence's end: copies of other pieces, which must not meet a zero of
+// Q or P where they hold Inf or NaN.  Each wave clears its own pieces, once they
+// have landed and before the barrier that shows them to the others.
+template <int D, int NUW, int CT, bool V16>
+__device__ __forceinline__ void clear_absent(const ChunkLoader<D, NUW, CT, V16>& f, int st, int valid) {
+  using G = Geo<D>;
+  typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+  const int p = f.lane % G::NCH;
+#pragma unroll
+  for (int v = 0; v < NUW; ++v) {
+    const int u = f.w * NUW + v;
+    const int r = u * G::RPI + f.lane / G::NCH;
+    const unsigned at = st * CT + u * 1024 + f.lane * 16;
+    if (r >= valid || swz_k<G::NCH>(r, p) >= G::DCH) *(lds_u32x4*)(size_t)(f.ks_base + at) = u32x4{};
+    if (r >= valid || (V16 ? swz_v16<G::NCH>(r, p) : swz_v<G::NCH>(r, p)) >= G::DCH)
+      *(lds_u32x4*)(size_t)(f.vs_base + at) = u32x4{};
+  }
+}
+
 // Per-lane LDS offset of the transpose reads of column tile dt (columns
 // dt*32 ..) of a V-swizzled tile: row (kk*16 + hf*4 + n16/4 [+8]), piece
 // dt*4 + (g16&1)*2 + (n16&3)/2; only dt interacts with the swizzle.  The

@@ -138,6 +138,48 @@ def test_overflow_is_walked_again(D, S, H):
     _check(out, lse, f64, lambda h, i: rows(i), S, scale_of(wl), [(h, i) for h in {0, H - 1} for i in range(nb)])
 
 
+@pytest.mark.parametrize("D,S,H", [(112, 64, 2), (112, 128, 2), (112, 64, 40), (112, 128, 40), (64, 64, 2),
+                                   (128, 128, 40)])
+def test_infinite_keys_and_values(D, S, H):
+    """Keys with -Inf in one of the first eight channels (the piece that stands in
+    for the padding of D = 112) against queries that are positive there: logits of
+    -Inf, weight zero.  Then an Inf in V at the first row of the last chunk (which
+    stands in for the rows past the end): that channel is Inf, the others finite.
+    In calls of 30 and of 600 query tiles."""
+    N = 901
+    wl = SC(f"routes_inf_{D}_{S}_{H}", 1, H, D, (1, 1, N), S, "topk", topk=1, seed=540)
+    f = {n: inputs.bf16_bits_to_f32(x).copy() for n, x in inputs.generate(wl).items()}
+    f["q"][..., 3] = np.abs(f["q"][..., 3]) + 0.5
+    f["k"][0, :, [40, 130, 900], 3] = -np.inf
+    nb = -(-N // S)
+    rows = lambda i: [0, min(130, N - 1) // S, nb - 1] if i % 2 else [nb - 1, 0]   # noqa: E731
+    idx, cnt = _arrays(rows, H, nb, 4)
+    prob, every = sva.problem_for(wl), lambda h, i: range(nb)
+    say(f"[routes inf D={D} S={S} H={H}]")
+
+    def run(v):
+        bits = {n: inputs._round_bf16(x) for n, x in dict(f, v=v).items()}
+        dev = device_inputs(bits)
+        got = [sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], idx, cnt, want_lse=True),
+               sva.dense_attention(prob, dev["q"], dev["k"], dev["v"], want_lse=True)]
+        torch.cuda.synchronize()
+        return got, {n: oracle.bf16_bits_to_f64(bits[n]) for n in ("q", "k", "v")}
+
+    sample = [(h, i) for h in {0, H - 1} for i in range(nb)]
+    got, f64 = run(f["v"])
+    for (out, lse), lists in zip(got, (lambda h, i: rows(i), every)):
+        _check(out, lse, f64, lists, S, scale_of(wl), sample)
+    v = f["v"].copy()
+    v[0, :, N // 32 * 32, 5] = np.inf
+    got, f64 = run(v)
+    f64["v"][0, :, N // 32 * 32, 5] = 0.0            # the other channels of the oracle
+    for (out, lse), lists in zip(got, (lambda h, i: rows(i), every)):
+        assert torch.isposinf(out[..., 5]).all()
+        out[..., 5] = 0
+        f64["v"][..., 5] = 0.0
+        _check(out, lse, f64, lists, S, scale_of(wl), sample)
+
+
 def test_pairs_of_long_sequences():
     """512 key blocks and row length 512: the block-pair kernel.  Ascending lists
     must match the single-block kernel (the same lists in short rows) bit for
