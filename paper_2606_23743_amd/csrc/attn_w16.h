@@ -273,7 +273,7 @@ __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& 
   for (int half = 0; half < QT; ++half) {
     bf16x8 qop[1][Geo16<D>::KS];
     load_q16<D>(qop, a.q + head, qbase + half * 16, mine ? N : 0, lane);
-    float m_run[1] = {-INFINITY}, l_part[1] = {0.0f};
+    float m_run[1] = {-INFINITY}, m_use[1] = {0.0f}, l_part[1] = {0.0f};
     f32x4 oacc[Geo16<D>::DT][1];
 #pragma unroll
     for (int dt = 0; dt < Geo16<D>::DT; ++dt) oacc[dt][0] = f32x4{};
@@ -305,13 +305,14 @@ __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& 
               for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[k2][0][r]);
           } else {
             bf16x8 pop[1];
-            softmax16(s, pop, l_part, m_run, a.scale_log2);
+            softmax16(s, pop, l_part, m_use, a.scale_log2);
             pv16<D>(pop, vs, voff, oacc);
           }
         }
         if (pass == 0) {
           const float m_new = fmaxf(m_run[0], quad_max(mx) * a.scale_log2);
-          const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_new);
+          m_use[0] = m_new == -INFINITY ? 0.0f : m_new;   // only logits of -Inf so far: weights of zero
+          const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_use[0]);
           m_run[0] = m_new;
           l_part[0] *= alpha;
 #pragma unroll

@@ -145,14 +145,16 @@ def test_infinite_keys_and_values(D, S, H):
     for the padding of D = 112) against queries that are positive there: logits of
     -Inf, weight zero.  Then an Inf in V at the first row of the last chunk (which
     stands in for the rows past the end): that channel is Inf, the others finite.
+    Some lists begin with a block of which every key is -Inf.
     In calls of 30 and of 600 query tiles."""
     N = 901
     wl = SC(f"routes_inf_{D}_{S}_{H}", 1, H, D, (1, 1, N), S, "topk", topk=1, seed=540)
     f = {n: inputs.bf16_bits_to_f32(x).copy() for n, x in inputs.generate(wl).items()}
     f["q"][..., 3] = np.abs(f["q"][..., 3]) + 0.5
     f["k"][0, :, [40, 130, 900], 3] = -np.inf
+    f["k"][0, :, 5 * S:6 * S, 3] = -np.inf
     nb = -(-N // S)
-    rows = lambda i: [0, min(130, N - 1) // S, nb - 1] if i % 2 else [nb - 1, 0]   # noqa: E731
+    rows = lambda i: [[nb - 1, 0], [0, 130 // S, nb - 1], [5, 0, nb - 1]][i % 3]   # noqa: E731
     idx, cnt = _arrays(rows, H, nb, 4)
     prob, every = sva.problem_for(wl), lambda h, i: range(nb)
     say(f"[routes inf D={D} S={S} H={H}]")
