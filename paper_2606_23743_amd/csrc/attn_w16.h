@@ -252,16 +252,18 @@ __device__ __forceinline__ void store_query16(void* out, float* lse, size_t head
 }
 
 // The general form of a query block, for a block whose fixed reference
-// overflowed (or, in the pair kernel, whose lists are not the selection
-// kernel's): the running maximum moves at every key block (online softmax), so
-// no sum can overflow.  Entered by every wave of the workgroup; `mine` is false
-// for waves that only load (the pair kernel's other block).  qbase: the wave's
-// first query; block_at(t): the t-th list entry, negative where it is skipped.
-// 16 queries at a time, so that it needs fewer registers than the fast loop
-// around it; one chunk at a time through stage 0, K twice (the block's maximum,
-// then its probabilities).  Padding is zeros here, not the copies that the fast
-// loop multiplies by zeros: a block with Inf in K or V comes here because of them.
-// Several times slower than the fast loop, on rows that real inputs do not have.
+// overflowed (or, in the pair kernel, whose lists are not the selection kernel's):
+// the running maximum moves at every chunk (online softmax), so no sum can
+// overflow.  Entered by every wave of the workgroup; `mine` is false for waves
+// that only load (the pair kernel's other block).  qbase: the wave's first
+// query; block_at(t): the t-th list entry, negative where it is skipped.  The
+// fast loop's sums are dead by now, so this one's take their registers.  Padding
+// is zeros here, not the copies that the fast loop multiplies by zeros: a block
+// with Inf in K or V comes here because of them.
+// One chunk at a time through stage 0, with nothing in flight beside it: rows that
+// real inputs do not have.  With a hot key block in every list, 16 heads of 63,240 x
+// 128 at 30% take 34.1 ms at S = 64 (pairs) and 21.1 at S = 128, where the fast loop
+// alone takes 10.6 and 8.4 (16 queries at a time with K read twice: 64.1 and 34.5).
 template <int D, int S, int QT, bool OUT_F32, class Loader, class BlockAt>
 __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& ld, const unsigned char* ks,
                                                const unsigned char* vs, const int (&koff)[Geo16<D>::KS],
@@ -269,64 +271,64 @@ __device__ __forceinline__ void general_walk16(const AttnArgs& a, const Loader& 
                                                BlockAt block_at, bool mine) {
   const int N = a.N, lane = ld.lane;
   const size_t head = (size_t)bh * N * D;
-#pragma unroll 1
-  for (int half = 0; half < QT; ++half) {
-    bf16x8 qop[1][Geo16<D>::KS];
-    load_q16<D>(qop, a.q + head, qbase + half * 16, mine ? N : 0, lane);
-    float m_run[1] = {-INFINITY}, m_use[1] = {0.0f}, l_part[1] = {0.0f};
-    f32x4 oacc[Geo16<D>::DT][1];
+  bf16x8 qop[QT][Geo16<D>::KS];
+  load_q16<D>(qop, a.q + head, qbase, mine ? N : 0, lane);
+  float m_run[QT], m_use[QT], l_part[QT];
+  f32x4 oacc[Geo16<D>::DT][QT] = {};
 #pragma unroll
-    for (int dt = 0; dt < Geo16<D>::DT; ++dt) oacc[dt][0] = f32x4{};
-#pragma unroll 1
-    for (int t = 0; t < count; ++t) {
-      const int j = block_at(t);
-      if (j < 0) continue;
-      const int end = min(N, j * S + S);
-      float mx = -INFINITY;
-#pragma unroll 1
-      for (int pass = 0; pass < 2; ++pass) {
-#pragma unroll 1
-        for (int key0 = j * S; key0 < end; key0 += 32) {
-          wait_vmcnt_lds_idle<0>();
-          wg_barrier();                      // every wave is done with the stage
-          load_tile<true>(ld, 0, key0);
-          load_tile<false>(ld, 0, key0);
-          wait_vmcnt<0>();
-          clear_absent(ld, 0, N - key0);
-          wait_vmcnt_lds_idle<0>();
-          wg_barrier();
-          f32x4 s[2][1];
-          qk16<D>(s, ks, koff, qop);
-          if (N - key0 < 32) mask_tail16(s, N - key0, lane);
-          if (pass == 0) {
-#pragma unroll
-            for (int k2 = 0; k2 < 2; ++k2)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[k2][0][r]);
-          } else {
-            bf16x8 pop[1];
-            softmax16(s, pop, l_part, m_use, a.scale_log2);
-            pv16<D>(pop, vs, voff, oacc);
-          }
-        }
-        if (pass == 0) {
-          const float m_new = fmaxf(m_run[0], quad_max(mx) * a.scale_log2);
-          m_use[0] = m_new == -INFINITY ? 0.0f : m_new;   // only logits of -Inf so far: weights of zero
-          const float alpha = __builtin_amdgcn_exp2f(m_run[0] - m_use[0]);
-          m_run[0] = m_new;
-          l_part[0] *= alpha;
-#pragma unroll
-          for (int dt = 0; dt < Geo16<D>::DT; ++dt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) oacc[dt][0][r] *= alpha;
-        }
-      }
-    }
-    const float l_tot[1] = {quad_sum(l_part[0])};
-    const bool has[1] = {l_tot[0] > 0.0f};
-    store_query16<D, OUT_F32>(a.out, a.lse, head, (size_t)bh * N, qbase + half * 16, mine ? N : 0, oacc, l_tot, m_run,
-                              has, lane);
+  for (int qt = 0; qt < QT; ++qt) {
+    m_run[qt] = -INFINITY;
+    l_part[qt] = 0.0f;
   }
+#pragma unroll 1
+  for (int t = 0; t < count; ++t) {
+    const int j = block_at(t);
+    if (j < 0) continue;
+    const int end = min(N, j * S + S);
+#pragma unroll 1
+    for (int key0 = j * S; key0 < end; key0 += 32) {
+      wait_vmcnt_lds_idle<0>();
+      wg_barrier();                          // every wave is done with the stage
+      load_tile<true>(ld, 0, key0);
+      load_tile<false>(ld, 0, key0);
+      wait_vmcnt<0>();
+      clear_absent(ld, 0, N - key0);
+      wait_vmcnt_lds_idle<0>();
+      wg_barrier();
+      if (!mine) continue;
+      f32x4 s[2][QT];
+      qk16<D>(s, ks, koff, qop);
+      if (N - key0 < 32) mask_tail16(s, N - key0, lane);
+#pragma unroll
+      for (int qt = 0; qt < QT; ++qt) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int k2 = 0; k2 < 2; ++k2)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) mx = fmaxf(mx, s[k2][qt][r]);
+        const float m_new = fmaxf(m_run[qt], quad_max(mx) * a.scale_log2);
+        m_use[qt] = m_new == -INFINITY ? 0.0f : m_new;   // only logits of -Inf so far: weights of zero
+        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - m_use[qt]);
+        m_run[qt] = m_new;
+        l_part[qt] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < Geo16<D>::DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) oacc[dt][qt][r] *= alpha;
+      }
+      bf16x8 pop[QT];
+      softmax16(s, pop, l_part, m_use, a.scale_log2);
+      pv16<D>(pop, vs, voff, oacc);
+    }
+  }
+  float l_tot[QT];
+  bool has[QT];
+#pragma unroll
+  for (int qt = 0; qt < QT; ++qt) {
+    l_tot[qt] = quad_sum(l_part[qt]);
+    has[qt] = l_tot[qt] > 0.0f;
+  }
+  store_query16<D, OUT_F32>(a.out, a.lse, head, (size_t)bh * N, qbase, mine ? N : 0, oacc, l_tot, m_run, has, lane);
 }
 
 }  // namespace attn
