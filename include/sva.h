@@ -180,10 +180,15 @@ int sva_select_blocks(const sva_problem* prob, const sva_select_params* sel,
  * float32.  Duplicate entries in a row are attended twice.
  * Performance: the fast kernels finish a query block in one pass; a block
  * whose row sums would overflow float32 (logits rising by more than about
- * 2^63 within one kept block), whose inputs hold Inf or NaN, or, at block 64
- * with D = 128 and long rows, whose pair of lists is not strictly increasing
- * and in range, is walked again by its workgroup with a running maximum
- * (correct, but several times slower per block).  Lists as sva_select_blocks writes them never take that path. */
+ * 2^63 within one kept block) or whose inputs hold Inf or NaN is walked again
+ * by its workgroup with a running maximum (correct, but several times slower
+ * per block); so are, at block 64 with D = 128 and long rows, two neighbouring
+ * query blocks whose lists are not strictly increasing and in range and hold
+ * more than 4096 entries together.  Lists as sva_select_blocks writes them
+ * never take that path.  Elsewhere (row sums below 2^64 times the largest
+ * weight of the row's first 32 keys) a query's result depends on its own head
+ * and list only: the same bits whatever the batch, the other heads and lists of
+ * the call and the row length kmax. */
 int sva_sparse_attention(const sva_problem* prob, const void* q, const void* k,
                          const void* v, const int32_t* kv_idx,
                          const int32_t* kv_count, int32_t kmax, void* out,

@@ -14,9 +14,12 @@
 // The union is built in LDS from two bitmaps over the key blocks, which needs
 // lists that are strictly increasing and in range, as the selection kernel
 // writes them.  A pair with any other list (out-of-range entries, repeats,
-// another order) skips the union and walks its two lists one after the other
-// with the general list semantics (general_walk16), as does a pair with a
-// query whose sum overflows.  Per chunk, the arithmetic of a wave is that of the
+// another order) walks its two lists one after the other instead of their union:
+// the same loop over entries of one block each, in list order, so a query's bits
+// are the single-block kernel's for every list.  Lists in falling order, 16
+// heads of 63,240 tokens at 30%: 14.5 ms, the single-block kernel 10.6 (a
+// walk with a running maximum took 24, before that 55).  Lists of more than 4096 entries together
+// and a query whose sum overflows take that walk (general_walk16).  Per chunk, the arithmetic of a wave is that of the
 // 32-query kernel (attn_w16.h: Sᵀ = K·Qᵀ on 16x16x32 products, fixed reference
 // maximum from the wave's first chunk, P rounded to bf16 with l summed from
 // it, Oᵀ += Vᵀ·Pᵀ), so keep-all lists give dense attention bit for bit.
@@ -27,7 +30,7 @@ namespace {
 
 using namespace attn;
 
-constexpr int kPairMaxBlocks = 4096;         // key blocks a pair's bitmaps and union hold
+constexpr int kPairMaxBlocks = 4096;         // key blocks a pair's bitmaps hold, and entries its union
 
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -98,8 +101,22 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
   }
   if (__builtin_amdgcn_ballot_w64(bad) != 0 && lane == 0) atomicOr(&list_bad, 1);
   __syncthreads();
-  const bool general = list_bad != 0;        // uniform
-  if (w == 0 && !general) {                  // compaction in block order, 64 words per step
+  if (w == 0 && list_bad) {                  // general lists: 2p's entries, then 2p+1's
+    int n = 0;
+    for (int s = 0; s < 2; ++s) {
+      const int32_t* idx = a.kv_idx + (size_t)(row0 + s) * a.kmax;
+      for (int t0 = 0; t0 < cnt2[s]; t0 += 64) {
+        const int t = t0 + lane;
+        const int j = t < cnt2[s] ? idx[t] : -1;
+        const bool ok = j >= 0 && j < nB;
+        const unsigned long long m = __builtin_amdgcn_ballot_w64(ok);
+        const int pos = n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+        if (ok && pos < kPairMaxBlocks) ulist[pos] = (uint16_t)((j << 2) | (1 << s));
+        n += __builtin_popcountll(m);
+      }
+    }
+    if (lane == 0) n_union = n;
+  } else if (w == 0) {                       // compaction in block order, 64 words per step
     int base = 0;
     for (int w0 = 0; w0 < words; w0 += 64) {
       const int wd = w0 + lane;
@@ -125,7 +142,8 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
     if (lane == 0) n_union = base;
   }
   __syncthreads();
-  const int U = general ? 0 : n_union;
+  const bool too_long = n_union > kPairMaxBlocks;   // uniform; general lists only
+  const int U = too_long ? 0 : n_union;
   auto ent = [&](int e) -> int {             // union entry e (block 0, kept by neither, past the end)
     return __builtin_amdgcn_readfirstlane(e < U ? (int)ulist[e] : 0);
   };
@@ -242,7 +260,7 @@ void attn_pair_kernel(AttnArgs a, int n_pairs) {
   const bool over = overflowed16<D>(l_tot, oacc);
   if (__builtin_amdgcn_ballot_w64(over) != 0 && lane == 0) atomicOr(&wg_bad, 1);
   __syncthreads();
-  if (general || wg_bad) {
+  if (too_long || wg_bad) {
 #pragma unroll 1
     for (int s = 0; s < (has_b ? 2 : 1); ++s) {
       const int row = row0 + s;

@@ -60,5 +60,14 @@ def flat_rows(kept):
     return [row for b in kept for h in b for row in h]
 
 
+def takes_pairs(heads, N, S, D, kmax) -> bool:
+    """Whether sparse attention of this call runs in the block-pair kernel: more
+    than 512 query tiles, 64-token blocks, D = 128, at most 4096 blocks, rows of
+    15% of the blocks or more, long rows of long sequences."""
+    nb = -(-N // S)
+    return (heads * -(-N // 64) > 512 and S == 64 and D == 128 and nb <= 4096 and 20 * kmax >= 3 * nb
+            and kmax * nb >= 160000)
+
+
 def scale_of(wl) -> float:
     return 1.0 / math.sqrt(wl.head_dim)

@@ -12,7 +12,7 @@ import paper_2606_23743_amd as sva
 from paper_2606_23743_amd import inputs, workloads
 
 from . import parity
-from .gpu_cases import device_inputs, say, scale_of
+from .gpu_cases import device_inputs, say, scale_of, takes_pairs
 
 pytestmark = pytest.mark.gpu
 
@@ -182,42 +182,47 @@ def test_infinite_keys_and_values(D, S, H):
         _check(out, lse, f64, lists, S, scale_of(wl), sample)
 
 
-def test_pairs_of_long_sequences():
-    """512 key blocks and row length 512: the block-pair kernel.  Ascending lists
-    must match the single-block kernel (the same lists in short rows) bit for
-    bit; pairs with general lists and with an overflowing block match the oracle."""
-    S, D, H, N = 64, 128, 2, 511 * 64 + 37
+@pytest.mark.parametrize("nb,dtype", [(902, "bf16"), (901, "bf16"), (901, "f32")])
+def test_pairs_of_long_sequences(nb, dtype):
+    """The block-pair kernel, the last pair with one block at 901.  Ascending and
+    general lists match the single-block kernel (the same lists in short rows) bit
+    for bit and the oracle; lists too long for a pair's union and overflowing
+    blocks match the oracle."""
+    S, D, H, N = 64, 128, 2, (nb - 1) * 64 + 37
+    say(f"[routes pairs nB={nb} {dtype}]")
     wl = SC("routes_pairs", 1, H, D, (1, 1, N), S, "topk", topk=1, seed=530)
     bits = inputs.generate(wl)
-    nb = -(-N // S)
-    assert nb * nb >= 160000                         # the pair rule's kmax * nB
+    assert takes_pairs(H, N, S, D, nb) and not takes_pairs(H, N, S, D, 12)
     rng = np.random.default_rng(5)
     asc = {i: sorted({int(j) for j in rng.integers(0, nb, 10)} | ({nb - 1} if i % 3 == 0 else set()))
            for i in range(nb)}
-    prob, f64 = sva.problem_for(wl), {n: oracle.bf16_bits_to_f64(bits[n]) for n in ("q", "k", "v")}
+    prob, f64 = sva.problem_for(wl, out_dtype=dtype), {n: oracle.bf16_bits_to_f64(bits[n]) for n in ("q", "k", "v")}
     dev = device_inputs(bits)
-    wide, cnt = _arrays(lambda i: asc[i], H, nb, nb)
-    o1, l1 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide, cnt, want_lse=True)
-    o2, l2 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide[..., :12].contiguous(), cnt, want_lse=True)
-    torch.cuda.synchronize()
-    assert H * nb > 512                              # 32 queries per wave
-    assert torch.equal(o1, o2) and torch.equal(l1, l2)
-    _check(o1, l1, f64, lambda h, i: asc[i], S, scale_of(wl), [(0, i) for i in (0, 1, 3, 256, nb - 2, nb - 1)])
+    for rows in (asc.__getitem__, _general_rows(nb, 12, rng)):
+        wide, cnt = _arrays(rows, H, nb, nb)
+        o1, l1 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide, cnt, want_lse=True)
+        o2, l2 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], wide[..., :12].contiguous(), cnt, want_lse=True)
+        torch.cuda.synchronize()
+        assert torch.equal(o1, o2) and torch.equal(l1, l2)
+        _check(o1, l1, f64, lambda h, i: rows(i), S, scale_of(wl), [(0, i) for i in list(range(14)) + [nb - 2, nb - 1]])
 
-    gen = _general_rows(nb, 12, rng)
-    idx, cnt = _arrays(gen, H, nb, nb)
+    many = {i: [int(j) for j in rng.integers(-1, nb, n)] for i, n in ((2, 2100), (3, 2100), (nb - 1, 4200))}
+    rows = lambda i: many.get(i, [i])   # noqa: E731
+    idx, cnt = _arrays(rows, H, nb, 4200)
     out, lse = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], idx, cnt, want_lse=True)
     torch.cuda.synchronize()
-    _check(out, lse, f64, lambda h, i: gen(i), S, scale_of(wl), [(0, i) for i in list(range(14)) + [nb - 2, nb - 1]])
+    _check(out, lse, f64, lambda h, i: rows(i), S, scale_of(wl), [(0, i) for i in (1, 2, 3, nb - 2, nb - 1)])
 
     f = {n: inputs.bf16_bits_to_f32(bits[n]).copy() for n in ("q", "k", "v")}
     f["k"][0, :, 0:64] *= 1e-3
     f["q"][0, :, 128:256] = 8.0                      # query blocks 2 and 3
+    f["q"][0, :, (nb - 1) * 64:] = 8.0               # and the last
     f["k"][0, :, 384:512] = 8.0                      # key blocks 6 and 7
     bits = {n: inputs._round_bf16(f[n]) for n in f}
     dev, f64 = device_inputs(bits), {n: oracle.bf16_bits_to_f64(bits[n]) for n in ("q", "k", "v")}
-    rows = lambda i: [0, 6, 7] if i in (2, 3, 5) else [0, 1]   # noqa: E731
+    rows = lambda i: [0, 6, 7] if i in (2, 3, 5, nb - 1) else [0, 1]   # noqa: E731
     idx, cnt = _arrays(rows, H, nb, nb)
     out, lse = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], idx, cnt, want_lse=True)
     torch.cuda.synchronize()
-    _check(out, lse, f64, lambda h, i: rows(i), S, scale_of(wl), [(0, i) for i in range(8)])
+    assert lse[0, 0, 128].item() > 400.0 and lse[0, 0, -1].item() > 400.0      # the regime this part is about
+    _check(out, lse, f64, lambda h, i: rows(i), S, scale_of(wl), [(0, i) for i in list(range(8)) + [nb - 2, nb - 1]])

@@ -14,7 +14,7 @@ import paper_2606_23743_amd as sva
 from paper_2606_23743_amd import inputs, workloads
 
 from . import parity
-from .gpu_cases import device_inputs, flat_rows, oracle_select, say, scale_of
+from .gpu_cases import device_inputs, flat_rows, oracle_select, say, scale_of, takes_pairs
 from .test_gpu_fp8 import _check_attention, _dequantised
 
 pytestmark = pytest.mark.gpu
@@ -171,7 +171,7 @@ def test_block_pairs_at_4096_blocks():
                                  scale_of(wl))
     kept, _ = oracle_select(wl, scores)
     oidx, ocnt = _kept_arrays(kept, nb)
-    assert oidx.shape[-1] * 20 >= 3 * nb                    # the pair path
+    assert takes_pairs(1, wl.seq_len, 64, 128, oidx.shape[-1])
     out, lse = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], oidx, ocnt, want_lse=True)
     torch.cuda.synchronize()
     rows = [0, 1, 2047, 4094, 4095]
@@ -188,10 +188,11 @@ def test_block_pairs_at_4096_blocks():
 
 def test_remainder_at_4096_blocks():
     """The first-order remainder at its largest block count, nB = 4096 (128
-    bitmap words per row, no padding rows, 4096-row weight chunks), on the
-    oracle's lists, sampled rows (first and last included) against the
+    bitmap words per row, no padding rows, 4096-row weight chunks; the kept
+    part in the block-pair kernel with float32 output), on the oracle's
+    lists, sampled rows (first and last included) against the
     oracle with the remainder's bounds."""
-    wl = SC("nb4096_remainder", 1, 1, 128, (4, 256, 256), 64, "topk", keep_ratio=0.05, seed=215)
+    wl = SC("nb4096_remainder", 1, 1, 128, (4, 256, 256), 64, "topk", keep_ratio=0.16, seed=215)
     bits = inputs.generate(wl)
     dev = device_inputs(bits)
     prob = sva.problem_for(wl)
@@ -202,6 +203,7 @@ def test_remainder_at_4096_blocks():
                                  scale_of(wl))
     kept, _ = oracle_select(wl, scores)
     oidx, ocnt = _kept_arrays(kept, nb)
+    assert takes_pairs(1, wl.seq_len, 64, 128, oidx.shape[-1])
     qp, kp = sva.pool_blocks(prob, dev["q"], dev["k"])
     out, lse = sva.sparse_attention_remainder(prob, dev["q"], dev["k"], dev["v"], qp, kp, oidx, ocnt, want_lse=True)
     torch.cuda.synchronize()

@@ -13,7 +13,7 @@ import paper_2606_23743_amd as sva
 from paper_2606_23743_amd import inputs, workloads
 
 from . import parity
-from .gpu_cases import (device_inputs, flat_rows, oracle_pool_all, oracle_select, say, scale_of)
+from .gpu_cases import device_inputs, flat_rows, oracle_pool_all, oracle_select, say, scale_of, takes_pairs
 
 pytestmark = pytest.mark.gpu
 
@@ -226,17 +226,17 @@ def test_keep_all_equals_dense_and_determinism(S):
 
 
 def test_block_pairs_match_single_blocks():
-    """At block 64 and D = 128, rows of at least 15% of the blocks (kmax) run
+    """At block 64 and D = 128, long rows of long sequences (kmax) run
     as pairs of neighbouring query blocks over the union of their lists;
     shorter rows one block at a time.  The same lists in longer rows (padded with -1 past the
     counts) take the pair path: outputs and LSE must match bit for bit, with an
     odd block count (the last pair has one block)."""
-    wl, bits, dev, prob = _small(seed=16, D=128, S=64, grid=(3, 10, 13), H=2)
+    wl, bits, dev, prob = _small(seed=16, D=128, S=64, grid=(1, 50, 1153), H=2)
     nb = sva.num_blocks(prob)
-    assert nb % 2 == 1
+    assert nb == 901
     qp, kp = sva.pool_blocks(prob, dev["q"], dev["k"])
     idx, cnt, _ = sva.select_blocks(prob, sva.select_topk(topk=1), qp, kp)
-    assert idx.shape[-1] * 20 < 3 * nb                      # single-block path
+    assert takes_pairs(2, wl.seq_len, 64, 128, nb) and not takes_pairs(2, wl.seq_len, 64, 128, idx.shape[-1])
     wide = torch.full((1, 2, nb, nb), -1, dtype=torch.int32, device="cuda")
     wide[..., :idx.shape[-1]] = idx
     o1, l1 = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], idx, cnt, want_lse=True)
@@ -343,10 +343,11 @@ def test_gradual_logit_growth_is_exact(S, D):
 def test_block_pair_overflow_is_recomputed():
     """The block-64 pair kernel (D = 128) with a later kept block whose logits
     exceed the first chunk's reference by about 1000 (log2 units): the pair
-    is marked and recomputed with per-iteration rescaling, and every query
-    block matches the oracle."""
+    is walked again with a running maximum, and the first eight query blocks
+    (the others keep nothing) match the oracle."""
     S, D = 64, 128
-    wl = SC("overflow_pairs", 1, 1, D, (4, 8, 16), S, "topk", topk=2, seed=33)   # N = 512, 8 blocks
+    wl = SC("overflow_pairs", 1, 1, D, (4, 15, 960), S, "topk", topk=2, seed=33)   # 900 blocks
+    nb = wl.seq_len // S
     bits = inputs.generate(wl)
     f = {n: inputs.bf16_bits_to_f32(bits[n]).copy() for n in ("q", "k", "v")}
     f["k"][0, 0, 0:64] *= 1e-3
@@ -356,20 +357,25 @@ def test_block_pair_overflow_is_recomputed():
     dev = device_inputs(new_bits)
     prob = sva.problem_for(wl)
     rows = [[0, 1], [1, 2], [0, 6], [0, 7], [3, 4], [4, 5], [5, 6], [6, 7]]
-    idx = np.array(rows, dtype=np.int32).reshape(1, 1, 8, 2)
-    cnt = np.full((1, 1, 8), 2, dtype=np.int32)
-    assert 2 * 20 >= 3 * 8                          # the pair path
+    idx = np.full((1, 1, nb, nb), -1, dtype=np.int32)
+    idx[0, 0, :8, :2] = rows
+    cnt = np.zeros((1, 1, nb), dtype=np.int32)
+    cnt[0, 0, :8] = 2
+    assert takes_pairs(1, wl.seq_len, S, D, nb)
     out, lse = sva.sparse_attention(prob, dev["q"], dev["k"], dev["v"], torch.from_numpy(idx).cuda(),
                                     torch.from_numpy(cnt).cuda(), want_lse=True)
     torch.cuda.synchronize()
     f64 = {n: oracle.bf16_bits_to_f64(new_bits[n]) for n in ("q", "k", "v")}
-    ref, rlse = oracle.block_sparse_attention(f64["q"], f64["k"], f64["v"], [[rows]], S, scale_of(wl))
-    assert rlse.max() > 400.0                        # the regime this test is about
+    ref, rlse = oracle.block_sparse_attention(f64["q"], f64["k"], f64["v"], [[rows + [[]] * (nb - 8)]], S, scale_of(wl),
+                                              rows=[(0, 0, i) for i in range(8)])
     o = out.float().cpu().numpy()
+    assert not o[0, 0, 8 * S:].any()
+    o, ref, rlse = o[0, 0, :8 * S], ref[0, 0, :8 * S], rlse[0, 0, :8 * S]
+    assert rlse.max() > 400.0                        # the regime this test is about
     assert np.isfinite(o).all()
     mx, mean = parity.attention_errors(o, ref, np.ones(ref.shape, dtype=bool))
     assert mx <= parity.MAX_ABS and mean <= parity.MEAN_ABS, (mx, mean)
-    err = np.abs(lse.cpu().numpy() - rlse)
+    err = np.abs(lse.cpu().numpy()[0, 0, :8 * S] - rlse)
     assert np.all(err <= parity.LSE_TOL + 1e-5 * np.abs(rlse)), err.max()
 
 
