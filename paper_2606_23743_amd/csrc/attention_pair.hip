@@ -292,19 +292,22 @@ hipError_t launch_pair(const Dims& d, const AttnArgs& a, hipStream_t stream) {
 
 // A pair stages each entry of the union once for two query blocks, at the price
 // of waves that sit idle while an entry of the other block is worked on.  That
-// pays where the single-block kernel is held by the bytes that miss the L2s
-// (about 6.3 of the 6.7 TB/s the fabric gives), which takes long rows of long
-// sequences: time of pairs over single blocks, by kmax * nB: 1.13-1.46 up to
-// 15,000 (N = 12,000), 1.14-1.25 at 42,000, 1.06-1.18 at 105,000 (N = 32,760),
-// 1.05 at 157,000, 1.02 at 225,000, 1.01-1.02 at 245,000 (N = 63,240 and 75,600),
-// 0.89-0.95 at 392,000, 0.87 at 350,000 (N = 75,600), 0.77 at 559,000, and on
-// mass lists with the first frame forced 0.986 at 166,000 (N = 46,662).  Rows of
-// under 15% of the blocks share too few with their neighbour (10% ran 8%
-// slower at N = 75,600).  At D = 112 pairs were level or slower at every
-// density.
+// pays where the single-block kernel is held by the bytes that miss the L2s,
+// which takes long rows of long sequences and a chip full of heads.  Time of
+// pairs over single blocks by kmax * nB, 32 heads: N = 63,240 top-k 1.03 at
+// 196,000, 1.005 at 245,000, 0.999 at 269,000, 0.99 at 294,000, 0.90 at 392,000; mass
+// lists (shorter than kmax) 1.00 at 196,000, 0.97 at 245,000, 0.95 at 294,000;
+// N = 75,600 top-k 1.03 at 210,000, 0.99 at 252,000, 0.89 at 350,000, mass 1.03 and
+// (280,000) 0.99.  16 heads: N = 111,600 0.88 at 457,000; N = 63,240 top-k 1.03-1.05
+// at 269,000, 0.98-1.00 at 392,000, mass 0.95-1.00 at 245,000; shorter sequences lose
+// longer (N = 46,656 top-k 1.07 at 266,000, 1.01 at 373,000; 57,304 1.07 at 281,000,
+// 0.92 at 563,000, mass 0.88 at 322,000), N = 32,760 up to its largest rows (1.05 at
+// 184,000).  Rows of under 15% of the blocks share too few with their neighbour
+// (10% ran 8% slower at N = 75,600).  At D = 112 pairs were level or slower at
+// every density.
 bool pair_attention_fits(const Dims& d, int kmax) {
   return d.S == 64 && d.D == 128 && d.nB <= kPairMaxBlocks && 20LL * kmax >= 3LL * d.nB &&
-         (int64_t)kmax * d.nB >= 160000;
+         (int64_t)kmax * d.nB >= 250000;
 }
 
 hipError_t launch_attention_pair(const Dims& d, const AttnArgs& a, hipStream_t stream) {

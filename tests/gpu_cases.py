@@ -66,7 +66,7 @@ def takes_pairs(heads, N, S, D, kmax) -> bool:
     15% of the blocks or more, long rows of long sequences."""
     nb = -(-N // S)
     return (heads * -(-N // 64) > 512 and S == 64 and D == 128 and nb <= 4096 and 20 * kmax >= 3 * nb
-            and kmax * nb >= 160000)
+            and kmax * nb >= 250000)
 
 
 def scale_of(wl) -> float:
