@@ -294,7 +294,8 @@ __global__ __launch_bounds__(kSegThreads) void token_bracket_kernel(const double
       need = k;
     } else if (pick[0] > 0) {
       blo = lo + ((uint64_t)(pick[0] - 1) << shift);
-      bhi = min(hi, blo + ((1ull << shift) - 1));
+      const uint64_t rest = (1ull << shift) - 1;            // keys of the bin past blo, 2^64 not crossed
+      bhi = hi - blo < rest ? hi : blo + rest;
       need = k - pick[1];
     } else {                                                // below it: fewer than k keys were counted
       blo = 0;

@@ -169,6 +169,33 @@ def test_select_score_distributions(N, r, kind):
     _check_select(bits, r, scores, kept_idx, kept_pos)
 
 
+@pytest.mark.parametrize("bits", [0x7FFF, 0x7FC0, 0x7F80])
+@pytest.mark.parametrize("r", [0.1, 0.25, 0.3, 0.5])
+def test_select_keeps_nan_and_inf_first(bits, r):
+    """30% of the tokens hold a NaN (of the widest payload: its order key lies
+    within a bin of 2^64; or the usual one) or an Inf: they rank above every
+    finite score, the lowest indices first."""
+    N, C = 3000, 16
+    rng = np.random.default_rng(int(1000 * r))
+    x = (rng.normal(size=(2, N, C)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    hot = np.stack([np.sort(rng.permutation(N)[: 3 * N // 10]) for _ in range(2)])
+    for b in range(2):
+        x[b, hot[b], 5] = bits
+    say(f"[token_prune bits={bits:#x} r={r}]")
+    scores, kept_idx, kept_pos = sva.token_select(_dev(x), r)
+    torch.cuda.synchronize()
+    k = otp.keep_count(N, r)
+    finite = scores.cpu().numpy()
+    for b in range(2):
+        finite[b, hot[b]] = -1.0
+        rest = np.argsort(-finite[b], kind="stable")[: max(0, k - len(hot[b]))]
+        want = np.sort(np.concatenate([hot[b][:k], rest]))
+        assert np.array_equal(kept_idx[b].cpu().numpy(), want)
+        pos = np.full(N, -1)
+        pos[want] = np.arange(k)
+        assert np.array_equal(kept_pos[b].cpu().numpy(), pos)
+
+
 def test_in_place_scatter_and_round_trip():
     """select -> gather -> scatter of the unchanged rows returns the input, in
     place over a copy of it as well."""
