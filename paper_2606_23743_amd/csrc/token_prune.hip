@@ -71,7 +71,6 @@ struct SelState {                // per batch entry, at the head of its workspac
   unsigned long long threshold;  // the k-th largest key
   unsigned long long lo, hi;     // its bin, inclusive
   unsigned long long kmin, kmax; // smallest and largest key in the bin
-  int need;                      // keys of the bin that are kept
   unsigned int cand;             // keys in the bin
   unsigned int ticket;           // workgroups finished in the current pass
   int need_eq;                   // keys equal to the threshold that are kept
@@ -287,24 +286,19 @@ __global__ __launch_bounds__(kSegThreads) void token_bracket_kernel(const double
   pick_bin(mine, k, red, pick);
   if (threadIdx.x == 0) {
     uint64_t blo, bhi;
-    int need;
     if (pick[0] == kBins - 1) {                             // above the bracket
       blo = hi + 1;
       bhi = ~0ull;
-      need = k;
     } else if (pick[0] > 0) {
       blo = lo + ((uint64_t)(pick[0] - 1) << shift);
       const uint64_t rest = (1ull << shift) - 1;            // keys of the bin past blo, 2^64 not crossed
       bhi = hi - blo < rest ? hi : blo + rest;
-      need = k - pick[1];
     } else {                                                // below it: fewer than k keys were counted
       blo = 0;
       bhi = lo - 1;
-      need = -1;                                            // known once the keys above are counted
     }
     w.st->lo = blo;
     w.st->hi = bhi;
-    w.st->need = need;
     w.st->ticket = 0;
   }
 }
