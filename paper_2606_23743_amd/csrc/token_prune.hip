@@ -15,6 +15,7 @@
 #include <mutex>
 
 #include "sva_internal.h"
+#include "token_bins.h"
 
 namespace sva {
 namespace {
@@ -39,22 +40,24 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Two passes over the scores instead of one per digit, because what such a pass
 // costs is not its reads (0.5 MB at 63,240 tokens) but its launch and the
 // hand-off to the last workgroup, 11-12 us together:
-//   bracket  every wave ranks the same 64 evenly spaced keys and takes a bracket
-//            that holds the k-th largest with 4 standard deviations to spare;
-//            the keys inside fall into 4094 equal bins (an LDS histogram per
-//            workgroup, flushed to the batch entry's), those above are counted;
-//            the last workgroup to finish (a ticket counter, no waiting) picks
-//            the bin of the k-th largest key.
+//   bins     64 sampled keys, sorted, are the splitters of 4096 bins (token_bins.h);
+//            every key is counted in its bin (an LDS histogram per workgroup,
+//            flushed to the batch entry's); the last workgroup to finish (a ticket
+//            counter, no waiting) picks the bin of the k-th largest key.
 //   resolve  per token segment: the keys above that bin and in it, the latter
 //            also listed (a few dozen of 63,240 tokens); the last workgroup
 //            finds the threshold among them and turns the counts into output
 //            offsets and tie quotas.
-// The rest is for scores that defeat the bracket (it missed, or one bin holds
-// more than kCand keys): a bin of one repeated key is its threshold as it
-// stands; otherwise the last workgroup runs a radix select over all keys by
-// itself.  Then the write pass emits kept_idx and kept_pos in token order.
-// Select of 63,240 tokens, everything after the scores: 90 us with six digit
-// passes and a counting pass, 38 us now.
+// A bin of one repeated key is its threshold as it stands.  One of more than kCand
+// different keys, which takes very many tokens whose scores crowd inside one
+// 64th of them, is left to a radix select over all keys by the last workgroup
+// alone.  Then the write pass emits kept_idx and kept_pos in token order.
+// Splitters, not equal bins over a bracket around the sampled k-th key: where
+// that bracket missed, or reached from rows of zeros to the scores of the others,
+// most keys fell into one bin.  63,240 tokens x 512, select in us, six digit passes
+// and a counting pass / bracket / splitters: 70 / 49 / 52 with random scores, 61 /
+// 224 / 50 with 30% zero rows, 66 / 193 / 46 for 32 frames of 30 x 52 with scores by
+// place (scores included, 14 us).
 
 constexpr int kDigitBits = 12;
 constexpr int kBins = 1 << kDigitBits;
@@ -190,33 +193,18 @@ __device__ bool last_to_finish(unsigned int* ticket, int* flag) {
   return last;
 }
 
-// the value that the wave's lane `src` holds
-__device__ __forceinline__ uint64_t lane_key(uint64_t v, int src) {
-  const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)v, src), hi = __builtin_amdgcn_readlane((uint32_t)(v >> 32), src);
-  return (uint64_t)hi << 32 | lo;
-}
-
-// The bracket [lo, hi] of the k-th largest of n keys from 64 evenly spaced ones
-// (each wave by itself; the same everywhere).  The rank of the threshold among
-// the 64 has standard deviation 8 sqrt(p (1 - p)), p = k / n; past the ends of
-// the sample the bracket goes on for the sample's own range.
-__device__ void sample_bracket(const double* s, int n, int k, uint64_t& lo, uint64_t& hi) {
+// the splitters: n keys' 64 samples in ascending order, by one wave
+__device__ void sort_samples(const double* s, int n, unsigned long long* sorted) {
   const int lane = threadIdx.x & 63;
-  const uint64_t key = order_key(s[(int)((int64_t)lane * n >> 6)]);
-  int pos = 0;                                              // place in descending order
+  const uint64_t key = order_key(s[sample_index(lane, n)]);
+  int pos = 0;
 #pragma unroll 8
   for (int j = 0; j < 64; ++j) {
-    const uint64_t o = lane_key(key, j);
-    pos += (o > key || (o == key && j < lane)) ? 1 : 0;
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)key, j), hi = __builtin_amdgcn_readlane((uint32_t)(key >> 32), j);
+    const uint64_t o = (uint64_t)hi << 32 | lo;
+    pos += (o < key || (o == key && j < lane)) ? 1 : 0;
   }
-  auto at = [&](int i) { return lane_key(key, __builtin_ctzll(__builtin_amdgcn_ballot_w64(pos == i))); };
-  const float p = (float)k / (float)n;
-  const float mid = 64.0f * p, margin = 32.0f * sqrtf(fmaxf(p * (1.0f - p), 0.0f)) + 1.0f;
-  const int ih = __builtin_amdgcn_readfirstlane((int)floorf(mid - margin));
-  const int il = __builtin_amdgcn_readfirstlane((int)ceilf(mid + margin));
-  const uint64_t first = at(0), last = at(63), range = first - last;
-  hi = ih >= 0 ? at(min(ih, 63)) : (first + range < first ? ~0ull : first + range);
-  lo = il <= 63 ? at(max(il, 0)) : (last < range ? 0 : last - range);
+  sorted[pos] = key;
 }
 
 // the bin (from the top) that holds the need-th largest of the counted keys: pick
@@ -245,34 +233,24 @@ __device__ void pick_bin(const uint32_t (&mine)[kBins / kSegThreads], int need, 
 }
 
 // grid (segments, B)
-__global__ __launch_bounds__(kSegThreads) void token_bracket_kernel(const double* __restrict__ scores,
-                                                                    unsigned char* __restrict__ ws,
-                                                                    int N, int seg_len, int k) {
+__global__ __launch_bounds__(kSegThreads) void token_bins_kernel(const double* __restrict__ scores,
+                                                                 unsigned char* __restrict__ ws,
+                                                                 int N, int seg_len, int k) {
   __shared__ uint32_t h[kBins];
+  __shared__ unsigned long long splitters[kSamples];
   __shared__ int red[kSegThreads / 64];
   __shared__ int flag;
   __shared__ int pick[3];
+  static_assert(kKeyBins <= kBins, "bins");
   const int b = blockIdx.y;
   const SelWs w = sel_ws(ws, b);
   for (int i = threadIdx.x; i < kBins; i += kSegThreads) h[i] = 0;
   const double* s = scores + (size_t)b * N;
-  uint64_t lo, hi;
-  sample_bracket(s, N, k, lo, hi);
-  // bins 1 .. kBins - 2 cover [lo, hi]; the top bin takes what is above
-  const int bits = hi > lo ? 64 - __builtin_clzll(hi - lo) : 0;
-  int shift = max(0, bits - kDigitBits);
-  if (((hi - lo) >> shift) > kBins - 3) ++shift;
+  if (threadIdx.x < 64) sort_samples(s, N, splitters);
   __syncthreads();
+  const KeyBins bins = make_bins(splitters, N, k);
   const int n0 = blockIdx.x * seg_len, n1 = min(N, n0 + seg_len);
-  int above = 0;
-  for (int n = n0 + threadIdx.x; n < n1; n += kSegThreads) {
-    const uint64_t key = order_key(s[n]);
-    if (key > hi) ++above;
-    else if (key >= lo) atomicAdd(&h[1 + (int)((key - lo) >> shift)], 1u);
-  }
-  int all_above;
-  block_scan(above, red, all_above);                        // (the barriers also close the histogram)
-  if (threadIdx.x == 0) h[kBins - 1] = (uint32_t)all_above;
+  for (int n = n0 + threadIdx.x; n < n1; n += kSegThreads) atomicAdd(&h[key_bin(bins, order_key(s[n]))], 1u);
   __syncthreads();
   for (int i = threadIdx.x; i < kBins; i += kSegThreads)
     if (h[i]) atomicAdd(&w.hist[i], h[i]);
@@ -285,20 +263,10 @@ __global__ __launch_bounds__(kSegThreads) void token_bracket_kernel(const double
     mine[e] = __hip_atomic_load(&w.hist[threadIdx.x * BPT + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   pick_bin(mine, k, red, pick);
   if (threadIdx.x == 0) {
-    uint64_t blo, bhi;
-    if (pick[0] == kBins - 1) {                             // above the bracket
-      blo = hi + 1;
-      bhi = ~0ull;
-    } else if (pick[0] > 0) {
-      blo = lo + ((uint64_t)(pick[0] - 1) << shift);
-      const uint64_t rest = (1ull << shift) - 1;            // keys of the bin past blo, 2^64 not crossed
-      bhi = hi - blo < rest ? hi : blo + rest;
-    } else {                                                // below it: fewer than k keys were counted
-      blo = 0;
-      bhi = lo - 1;
-    }
-    w.st->lo = blo;
-    w.st->hi = bhi;
+    uint64_t lo, hi;
+    bin_range(bins, pick[0], lo, hi);                       // every key was counted: a bin holds the k-th
+    w.st->lo = lo;
+    w.st->hi = hi;
     w.st->ticket = 0;
   }
 }
@@ -617,7 +585,7 @@ hipError_t launch_token_select(int B, int N, int C, int k, const uint16_t* x, do
   if (e != hipSuccess) return e;
   const int nseg = token_select_segments(N);
   const int seg_len = (N + nseg - 1) / nseg;
-  hipLaunchKernelGGL(token_bracket_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N, seg_len, k);
+  hipLaunchKernelGGL(token_bins_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N, seg_len, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(token_resolve_kernel, dim3(nseg, B), dim3(kSegThreads), 0, stream, scores, ws, N, seg_len, k);
   if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -143,11 +143,13 @@ def test_ties_across_segments():
     (30000, 0.5, "cluster"),       # 18000 of them: more than the list holds, all keys by one workgroup
     (30000, 0.59995, "cluster"),   # the cut just above the zero rows
     (30000, 0.7, "cluster"),       # inside the zero rows
-    (30000, 3e-4, "outliers"),     # the cut above the sampled bracket
-    (30000, 0.9998, "outliers"),   # below it
+    (30000, 3e-4, "outliers"),     # the cut above every sample
+    (30000, 0.9998, "outliers"),   # below every sample
     (30000, 1.0, "outliers"),
     (2048 * 3 + 1, 0.5, "plain"),  # a segment of one token more
     (64, 0.5, "plain"), (65, 0.99, "plain"),
+    (32 * 780, 0.5, "frames"),     # scores by place in the frame, 32 frames
+    (300000, 0.5, "cluster"),      # 2800 different keys between two samples, 180,000 within 1%
 ])
 def test_select_score_distributions(N, r, kind):
     C = 16
@@ -159,6 +161,8 @@ def test_select_score_distributions(N, r, kind):
         x[:, live, 1:] = rng.normal(size=(2, len(live), C - 1)) * 0.02
     else:
         x[:] = rng.normal(size=x.shape)
+        if kind == "frames":
+            x *= np.tile(np.exp(0.5 * rng.normal(size=780)), N // 780)[None, :, None]
         if kind == "outliers":
             x[:, rng.permutation(N)[:20]] *= 2.0 ** 30
             x[:, rng.permutation(N)[:20]] *= 2.0 ** -30
