@@ -30,7 +30,7 @@
 // reciprocal root, one table offset per token and axis and no waits between the
 // rows, 32 heads of 63,240 x 128 take 353 us instead of 468 (5.9 TB/s instead of
 // 4.4), 48 of 111,600 x 128 0.90-0.94 ms instead of 1.08 (5.9-6.1 TB/s instead of
-// 5.1; the first twenty calls after a pause 1.02-1.09 on average).
+// 5.1; the first twenty calls after a pause 1.02-1.11 on average).
 #include <type_traits>
 
 #include "sva_internal.h"
