@@ -252,7 +252,7 @@ __device__ __forceinline__ void store_query16(void* out, float* lse, size_t head
 }
 
 // The general form of a query block, for a block whose fixed reference
-// overflowed (or, in the pair kernel, whose lists are not the selection kernel's):
+// overflowed (or, in the pair kernel, whose lists are too long for its union):
 // the running maximum moves at every chunk (online softmax), so no sum can
 // overflow.  Entered by every wave of the workgroup; `mine` is false for waves
 // that only load (the pair kernel's other block).  qbase: the wave's first
